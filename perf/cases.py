@@ -1,0 +1,421 @@
+"""The calls whose speed is measured: access plans, decode over a selected
+view, verify windows over the full KV, and the calls around them (acceptance,
+KV append, view compaction).
+
+A case is a dict of plain values. ``op`` names the call; the sizes of the
+inputs (sequence lengths included) follow from the case alone, their values
+from the seed. The pools, tables and queries are drawn here with torch and
+numpy; ``run`` goes through the package's binding, with calls marshalled once
+where the binding offers that (``bind_*``), as the executor does.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_2607_24260_amd import kap as K
+
+PAGE = 16
+DEV = "cuda"
+ELEM = {"f32": 4, "bf16": 2, "fp8": 1}
+
+
+def _attn(name, op, batch, seq, kv, *, hq=32, hkv=8, dim=128, ragged=False, frac=1.0,
+          scheduled=False, tokens=False, window=1):
+    c = {"op": op, "batch": batch, "seq": seq, "ragged": ragged, "kv": kv, "hq": hq, "hkv": hkv,
+         "dim": dim, "frac": frac, "scheduled": scheduled, "tokens": tokens, "window": window}
+    return {"name": name, **c} if name else c
+
+
+def listed():
+    return [
+        # One plan per request batch before its proposal steps: 4 requests of
+        # 128K tokens with 128 ranked evidence spans each, 5.5% kept. Latency.
+        {"name": "plan_128k", "op": "plan", "batch": 4, "seq": 131072, "ragged": False,
+         "spans": 128, "frac": 0.055, "tokens": False},
+        # The smallest request: one 4K sequence kept in float32 (reference
+        # serving), a proposal step on 28% of it ...
+        _attn("decode_4k_f32", "decode", 1, 4096, "f32", frac=0.28),
+        # ... and its 5-token verify window over everything.
+        _attn("verify_4k_f32", "verify", 1, 4096, "f32", window=5),
+        # Proposal step of a mid-size batch: 8 sequences of 16K, 15% views.
+        _attn("decode_16k", "decode", 8, 16384, "bf16", frac=0.15),
+        # The headline: 4 sequences of 128K, 5.5% views; the view is fixed over
+        # the steps of a cycle, so the step runs from its schedule.
+        _attn("decode_128k", "decode", 4, 131072, "bf16", frac=0.055, scheduled=True),
+        # Its 5-token verify window over the full context.
+        _attn("verify_128k", "verify", 4, 131072, "bf16", window=5),
+        # A serving batch after fallback: 64 sequences of 4K-128K on full
+        # context, fp8 KV with a scale per page.
+        _attn("decode_ragged_fp8", "decode", 64, 131072, "fp8", ragged=True),
+        # The longest verify window of that batch's proposal lengths (8 + 1).
+        _attn("verify_ragged_fp8", "verify", 64, 131072, "fp8", ragged=True, window=9),
+        # Models with another head layout: eight query heads per KV head ...
+        _attn("decode_gqa8", "decode", 8, 32768, "bf16", hq=32, hkv=4, frac=0.15),
+        # ... and 64-dim heads, two query heads per KV head, 5-token windows.
+        _attn("verify_d64", "verify", 8, 16384, "bf16", hq=16, hkv=8, dim=64, window=5),
+        # Acceptance of 64 five-token windows over a 151936-token vocabulary.
+        {"name": "accept_64x5", "op": "accept", "batch": 64, "window": 5, "vocab": 151936,
+         "logits": "bf16"},
+        # A chunked-prefill step: 4 sequences' next 2048 tokens into their pages.
+        {"name": "append_prefill", "op": "append", "batch": 4, "new": 2048, "kv": "bf16",
+         "hkv": 8, "dim": 128},
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    op = rng.choices(["plan", "decode", "verify", "accept", "append", "compact"],
+                     [3, 7, 6, 1, 2, 1])[0]
+    if op == "plan":
+        return {"op": op, "batch": _log(rng, 1, 64), "seq": _log(rng, 2048, 262144),
+                "ragged": rng.random() < 0.5, "spans": _log(rng, 8, 2000),
+                "frac": round(rng.uniform(0.03, 0.4), 4), "tokens": rng.random() < 0.3}
+    if op == "accept":
+        return {"op": op, "batch": _log(rng, 1, 96), "window": rng.randint(2, 9),
+                "vocab": _log(rng, 32000, 160000), "logits": rng.choice(["bf16", "f32"])}
+    # half of the draws: the layout of the main path (four 128-dim query heads
+    # per KV head); the rest over the other layouts
+    if rng.random() < 0.5:
+        hkv, group, dim, kv = rng.choice([2, 4, 8]), 4, 128, rng.choice(["bf16", "fp8"])
+        most = 2 << 30                          # bytes of KV
+    else:
+        most = 512 << 20
+        hkv, group = rng.choice([1, 2, 4, 8, 16]), rng.choice([1, 2, 3, 4, 6, 8, 16])
+        dim, kv = rng.choice([64, 128, 128, 256]), rng.choice(["bf16", "bf16", "fp8", "f32"])
+    token_bytes = 2 * hkv * dim * ELEM[kv]
+    if op == "append":
+        new = _log(rng, 1, 4096)
+        return {"op": op, "batch": min(_log(rng, 1, 32), max(1, (64 << 20) // (new * token_bytes))),
+                "new": new, "kv": kv, "hkv": hkv, "dim": dim}
+    seq = _log(rng, 700, 131072 if kv != "f32" else 32768)
+    batch = _log(rng, 1, 64)
+    seq = min(seq, most // token_bytes)
+    batch = max(1, min(batch, most // (seq * token_bytes)))
+    ragged = batch > 1 and rng.random() < 0.5
+    if op == "compact":
+        return {"op": op, "batch": batch, "seq": seq, "ragged": ragged, "kv": kv, "hkv": hkv,
+                "dim": dim, "frac": round(rng.uniform(0.03, 0.3), 4)}
+    if op == "verify":
+        return _attn(None, op, batch, seq, kv, hq=hkv * group, hkv=hkv, dim=dim, ragged=ragged,
+                     window=rng.choice([1, 2, 3, 3, 4, 5, 5, 6, 8, 9, 9, 12, 13, 16]))
+    frac = 1.0 if rng.random() < 0.3 else round(rng.uniform(0.03, 0.4), 4)
+    return _attn(None, op, batch, seq, kv, hq=hkv * group, hkv=hkv, dim=dim, ragged=ragged,
+                 frac=frac, scheduled=rng.random() < 0.5,
+                 tokens=frac < 1 and rng.random() < 0.25)
+
+
+# --------------------------------------------------------------------------
+# inputs
+# --------------------------------------------------------------------------
+
+def _lengths(c):
+    """Sequence lengths, from the case alone: all ``seq``, or log-uniform in
+    [seq / 32, seq] with the longest at ``seq``."""
+    if not c.get("ragged"):
+        return np.full(c["batch"], c["seq"], dtype=np.int32)
+    r = np.random.default_rng(c["seq"] * 131 + c["batch"])
+    lens = np.exp(r.uniform(math.log(max(1, c["seq"] // 32)), math.log(c["seq"]), c["batch"]))
+    lens = np.maximum(1, np.round(lens)).astype(np.int32)
+    lens[int(r.integers(0, c["batch"]))] = c["seq"]
+    return lens
+
+
+def _tables(r, lens):
+    """A shuffled physical page order: (pages, block table padded with -1)."""
+    npg = -(-lens.astype(np.int64) // PAGE)
+    perm = r.permutation(int(npg.sum())).astype(np.int32)
+    fbt = np.full((len(lens), int(npg.max())), -1, dtype=np.int32)
+    at = 0
+    for b, n in enumerate(npg):
+        fbt[b, :n] = perm[at:at + n]
+        at += int(n)
+    return int(npg.sum()), fbt
+
+
+def _spans(r, L, n):
+    """n candidate spans of 64-1024 tokens (fewer in short sequences), unaligned."""
+    hi = max(PAGE, min(1024, L // 4))
+    length = PAGE * np.maximum(1, np.round(r.uniform(min(64, hi), hi, n) / PAGE)).astype(np.int64)
+    start = np.floor(r.uniform(0, 1, n) * np.maximum(1, L - length + 1)).astype(np.int64)
+    return start.astype(np.int32), length.astype(np.int32), \
+        r.dirichlet(np.full(n, 0.5)).astype(np.float32)
+
+
+def _views(c, r, lens):
+    """Each sequence's selected tokens: a prefix, a suffix and ranked spans
+    until the budget is spent (whole pages, or tokens where ``tokens``); with
+    ``frac`` 1 the full context. [(logical pages ascending, 16-bit masks)]."""
+    views = []
+    for L in (int(x) for x in lens):
+        NP = -(-L // PAGE)
+        if c["frac"] >= 1.0:
+            views.append((np.arange(NP, dtype=np.int32), np.full(NP, 0xFFFF, np.int32)))
+            continue
+        budget, unit = int(c["frac"] * L), 1 if c["tokens"] else PAGE
+        seen = np.zeros(NP * PAGE, dtype=bool)
+        mark = lambda x, e: seen.__setitem__(slice(x // unit * unit, -(-e // unit) * unit), True)
+        mark(0, min(L, 256, budget // 4 + 1))
+        mark(max(0, L - min(128, budget // 4 + 1)), L)
+        used = int(seen.sum())
+        for st, ln, _ in zip(*_spans(r, L, 160)):
+            x, e = int(st) // unit * unit, -(-min(L, int(st) + int(ln)) // unit) * unit
+            cost = int((~seen[x:e]).sum())
+            if used + cost <= budget:
+                seen[x:e] = True
+                used += cost
+        bits = seen.reshape(NP, PAGE)
+        pages = np.nonzero(bits.any(1))[0].astype(np.int32)
+        views.append((pages, (bits[pages] @ (1 << np.arange(PAGE))).astype(np.int32)))
+    return views
+
+
+def _pool(c, pages, gen):
+    """K and V pools, iid N(0, 1); fp8: codes and a scale per page."""
+    kv, Hkv, D = c["kv"], c["hkv"], c["dim"]
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "fp8": torch.uint8}[kv]
+    k = torch.empty((pages, Hkv, D // 8, PAGE, 8), dtype=dt, device=DEV)
+    v = torch.empty((pages, Hkv, D, PAGE), dtype=dt, device=DEV)
+    scales = torch.empty((pages, 2), dtype=torch.float32, device=DEV) if kv == "fp8" else None
+    step = max(1, (256 << 20) // (Hkv * D * PAGE * 4))
+    for i, dst in enumerate((k, v)):
+        for p in range(0, pages, step):
+            part = dst[p:p + step]
+            if kv != "fp8":
+                part.normal_(generator=gen)
+                continue
+            x = torch.randn(part.shape, generator=gen, device=DEV)
+            s = x.abs().flatten(1).amax(1) / 448.0
+            scales[p:p + step, i] = s
+            x = (x / s.view(-1, *[1] * (x.dim() - 1))).clamp_(-448.0, 448.0)
+            part.copy_(x.to(torch.float8_e4m3fn).view(torch.uint8))
+    return k, v, scales
+
+
+def _i32(x):
+    return torch.as_tensor(np.ascontiguousarray(x, dtype=np.int32)).to(DEV)
+
+
+def _attn_inputs(c, seed):
+    """Pool, tables and queries of a decode, verify or compaction case."""
+    r = np.random.default_rng(seed)
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    lens = _lengths(c)
+    pages, fbt = _tables(r, lens)
+    s = {"lens": lens, "pages": pages, "fbt": fbt}
+    s["k"], s["v"], s["scales"] = _pool(c, pages, gen)
+    if c["op"] != "verify":
+        s["views"] = _views({"tokens": False, **c}, r, lens)
+    if c["op"] != "compact":
+        shape = (c["batch"], c["window"], c["hq"], c["dim"])
+        q = torch.randn(shape, generator=gen, device=DEV) / math.sqrt(c["dim"])
+        s["q"] = q.to(torch.float32 if c["kv"] == "f32" else torch.bfloat16)
+    return s
+
+
+def _view_tables(c, s):
+    """The views as block tables of a fixed capacity (the budget's pages and a
+    few more for the prefix and suffix): physical pages, logical pages, masks,
+    counts."""
+    B, cap = c["batch"], s["fbt"].shape[1]
+    if c["frac"] < 1.0:
+        cap = min(cap, math.ceil(c["frac"] * c["seq"] / PAGE) + 4)
+    bt, lb, mk = (np.zeros((B, cap), dtype=np.int32) for _ in range(3))
+    for b, (p, m) in enumerate(s["views"]):
+        bt[b, :len(p)], lb[b, :len(p)], mk[b, :len(p)] = s["fbt"][b][p], p, m
+    return _i32(bt), _i32(lb), _i32(mk), _i32([len(p) for p, _ in s["views"]]), cap
+
+
+def _workspace(n):
+    return torch.zeros(max(256, n), dtype=torch.uint8, device=DEV)
+
+
+def prepare(case, seed):
+    c, op = case, case["op"]
+    B = c["batch"]
+    if op == "plan":
+        r = np.random.default_rng(seed)
+        lens = _lengths(c)
+        pages, fbt = _tables(r, lens)
+        per = [_spans(r, int(L), c["spans"]) for L in lens]
+        cat = [np.concatenate(x) for x in zip(*per)]
+        cap = fbt.shape[1]
+        out = {n: torch.empty((B, cap), dtype=torch.int32, device=DEV)
+               for n in ("view_block_table", "view_logical_block")
+               + (("view_token_mask",) if c["tokens"] else ())}
+        out.update({n: torch.empty(B, dtype=torch.int32, device=DEV) for n in
+                    ("view_num_blocks", "view_tokens", "spans_taken", "plan_status")})
+        out["span_selected"] = torch.empty(len(cat[0]), dtype=torch.int32, device=DEV)
+        for t in out.values():          # entries past a view's end stay as they are
+            t.zero_()
+        budget = np.floor(c["frac"] * lens).astype(np.int32)
+        call = K.bind_compile_plan(
+            _i32(lens), _i32(fbt), _i32(np.arange(B + 1) * c["spans"]), _i32(cat[0]),
+            _i32(cat[1]), torch.as_tensor(cat[2]).to(DEV), _i32(np.full(B, 256)),
+            _i32(np.full(B, 128)), _i32(budget), num_pages=pages, view_capacity=cap, out=out,
+            workspace=_workspace(K.compile_plan_workspace_bytes(B, len(cat[0]), cap)),
+            token_granular=c["tokens"])
+        return {"call": call, "out": out}
+    if op == "accept":
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        dt = torch.float32 if c["logits"] == "f32" else torch.bfloat16
+        logits = (3 * torch.randn((B, c["window"], c["vocab"]), generator=gen, device=DEV)).to(dt)
+        # drafts of a proposer that mostly agrees: a token of the top 4
+        rank = torch.randint(0, 4, (B, c["window"] - 1, 1), generator=gen, device=DEV)
+        draft = logits[:, :-1].topk(4, dim=-1).indices.gather(2, rank)[..., 0]
+        lib = K.load_library()
+        return {"op": op, "logits": logits, "draft": draft.to(torch.int32).contiguous(),
+                "accepted": torch.empty(B, dtype=torch.int32, device=DEV),
+                "carry": torch.empty(B, dtype=torch.int32, device=DEV),
+                "ws": _workspace(int(lib.kap_accept_top3_workspace_bytes(B, c["window"])))}
+    if op == "append":
+        r = np.random.default_rng(seed)
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        # tokens each sequence already holds (sizes follow from the case alone)
+        done = np.random.default_rng(B * 131 + c["new"]).integers(0, 2000, B)
+        pages, fbt = _tables(r, done + c["new"])
+        pos = done[:, None] + np.arange(c["new"])
+        slot = np.take_along_axis(fbt, pos // PAGE, 1).astype(np.int64) * PAGE + pos % PAGE
+        k, v, scales = _pool(c, pages, gen)
+        new = [x.normal_(generator=gen) if c["kv"] != "fp8" else
+               x.random_(0, 127, generator=gen) for x in
+               (torch.empty((slot.size, c["hkv"], c["dim"]), dtype=k.dtype, device=DEV)
+                for _ in range(2))]
+        qd = torch.float32 if c["kv"] == "f32" else torch.bfloat16
+        return {"op": op, "kv": K.KVCache(k, v, c["hkv"], qd, scales), "new": new,
+                "slot": torch.as_tensor(slot.reshape(-1)).to(DEV)}
+    s = _attn_inputs(c, seed)
+    qd = torch.float32 if c["kv"] == "f32" else torch.bfloat16
+    kv = K.KVCache(s["k"], s["v"], c.get("hq", c["hkv"]), qd, s["scales"])
+    lens = _i32(s["lens"])
+    if op == "compact":
+        bt, _, _, nb, cap = _view_tables(c, s)
+        dst = K.KVCache(*(torch.zeros((B * cap,) + tuple(x.shape[1:]), dtype=x.dtype, device=DEV)
+                          for x in (s["k"], s["v"])), c["hkv"], qd,
+                        None if s["scales"] is None else
+                        torch.zeros((B * cap, 2), device=DEV))
+        return {"op": op, "src": kv, "dst": dst, "bt": bt, "nb": nb, "cap": cap,
+                "table": torch.empty((B, cap), dtype=torch.int32, device=DEV)}
+    shape = (B, c["window"], c["hq"], c["dim"]) if op == "verify" else (B, c["hq"], c["dim"])
+    out = torch.empty(shape, dtype=torch.float32, device=DEV)
+    lse = torch.empty(shape[:-1], dtype=torch.float32, device=DEV)
+    if op == "verify":
+        longest = int(s["lens"].max())
+        ws = _workspace(K.verify_workspace_bytes(kv, B, c["window"], longest))
+        call = K.bind_verify(kv, s["q"], lens, _i32(s["fbt"]), longest, 1.0, out, lse, ws)
+    else:
+        bt, lb, mk, nb, cap = _view_tables(c, s)
+        mk = mk if c["tokens"] else None
+        ws = _workspace(K.selected_decode_workspace_bytes(kv, B, cap))
+        plan = K.decode_schedule(kv, lens, bt, lb, nb, cap, view_token_mask=mk) \
+            if c["scheduled"] else None
+        call = K.bind_selected_decode(kv, s["q"][:, 0].contiguous(), lens, bt, lb, nb, cap, 1.0,
+                                      out, lse, ws, view_token_mask=mk, schedule=plan)
+    return {"call": call, "out": {"o": out, "lse": lse}}
+
+
+def run(state):
+    if "call" in state:
+        state["call"]()
+        return state["out"]
+    if state["op"] == "accept":
+        return K.accept_top3(state["logits"], state["draft"], 3, state["accepted"],
+                             state["carry"], state["ws"])
+    if state["op"] == "append":
+        kv = state["kv"]
+        K.append_kv(kv, *state["new"], state["slot"])
+        return {"k": kv.k_pages, "v": kv.v_pages}
+    dst = state["dst"]
+    K.compact_view(state["src"], state["bt"], state["nb"], state["cap"], dst, out=state["table"])
+    return {"k": dst.k_pages, "v": dst.v_pages, "table": state["table"]} | (
+        {} if dst.kv_scales is None else {"scales": dst.kv_scales})
+
+
+def work(case):
+    c, op = case, case["op"]
+    B = c["batch"]
+    if op == "plan":
+        lens, S = _lengths(c), B * c["spans"]
+        kept = float(np.floor(c["frac"] * lens / PAGE).sum())
+        # spans in, flags out; the view's block-table entries in, its tables out
+        return {"bytes": 16 * S + 4 * kept * (4 if c["tokens"] else 3) + 40 * B,
+                "flops": 0}
+    if op == "accept":
+        n = B * c["window"] * c["vocab"]
+        return {"bytes": n * (4 if c["logits"] == "f32" else 2) + 4 * B * (c["window"] + 1),
+                "flops": n}
+    token = 2 * c["hkv"] * c["dim"] * ELEM[c["kv"]]
+    if op == "append":
+        return {"bytes": B * c["new"] * (2 * token + 8), "flops": 0}
+    lens = _lengths(c).astype(np.int64)
+    frac = c.get("frac", 1.0)
+    tokens = float(np.floor(frac * lens).sum()) if frac < 1 else float(lens.sum())
+    pages = tokens / PAGE
+    if op == "compact":
+        return {"bytes": 2 * tokens * token + 8 * pages, "flops": 0}
+    rows = B * c["window"] * c["hq"]
+    q = 4 if c["kv"] == "f32" else 2
+    scales = 8 * pages if c["kv"] == "fp8" else 0
+    table = pages * (4 if op == "verify" else 12 if c["tokens"] else 8)
+    return {"bytes": tokens * token + scales + table + rows * (c["dim"] * (q + 4) + 4),
+            "flops": 4.0 * tokens * c["window"] * c["hq"] * c["dim"]}
+
+
+def tolerance(case):
+    if case["op"] not in ("decode", "verify"):
+        return "exact"                      # selections, counts and copied bits
+    # float32 outputs and sums. The main path's weights (bf16 / fp8, four
+    # 128-dim heads) carry 16 bits: 1e-5 from 64 bits; everywhere else weights
+    # are float32: 5e-7 at the listed sizes, more over longer sums.
+    main = case["kv"] != "f32" and case["dim"] == 128 and case["hq"] == 4 * case["hkv"]
+    return {"rel": 4e-5 if main else 1e-5}
+
+
+def exact(case, seed):
+    """Attention of decode and verify cases in 64 bits, one sequence at a time."""
+    c = case
+    if c["op"] not in ("decode", "verify"):
+        return None
+    s = _attn_inputs(c, seed)
+    B, W, Hq, Hkv, D = c["batch"], c["window"], c["hq"], c["hkv"], c["dim"]
+    out = torch.zeros((B, W, Hq, D), dtype=torch.float64, device=DEV)
+    lse = torch.zeros((B, W, Hq), dtype=torch.float64, device=DEV)
+
+    def tile(x, which, pages):              # stored pages -> values
+        if c["kv"] != "fp8":
+            return x[pages].double()
+        y = x[pages].view(torch.float8_e4m3fn).to(torch.float64)
+        return y * s["scales"][pages, which].double().view(-1, *[1] * (y.dim() - 1))
+
+    for b in range(B):
+        L = int(s["lens"][b])
+        if c["op"] == "verify":
+            logical = np.arange(-(-L // PAGE))
+            bits = np.full(len(logical), 0xFFFF)
+        else:
+            logical, bits = s["views"][b]
+            bits = bits if c["tokens"] else np.full(len(logical), 0xFFFF)
+        pages = torch.as_tensor(s["fbt"][b][logical].astype(np.int64)).to(DEV)
+        pos = torch.as_tensor((logical[:, None] * PAGE + np.arange(PAGE)).reshape(-1)).to(DEV)
+        shown = torch.as_tensor((bits[:, None] >> np.arange(PAGE) & 1).reshape(-1) > 0).to(DEV)
+        n = len(logical) * PAGE
+        last = torch.arange(W, device=DEV) + (L - W + 1) if c["op"] == "verify" else \
+            torch.full((1,), L, device=DEV)                     # row i sees positions < last[i]
+        see = shown[None] & (pos[None] < last[:, None])         # [W][n]
+        for g in range(Hkv):
+            k = tile(s["k"][:, g], 0, pages).permute(0, 2, 1, 3).reshape(n, D)
+            v = tile(s["v"][:, g], 1, pages).permute(0, 2, 1).reshape(n, D)
+            v = torch.where((pos < L)[:, None] & shown[:, None], v, 0.0)
+            h = slice(g * (Hq // Hkv), (g + 1) * (Hq // Hkv))
+            z = (s["q"][b, :, h].double().reshape(-1, D) @ k.T).view(W, -1, n)
+            z = torch.where(see[:, None], z, -math.inf)
+            lse[b, :, h] = torch.logsumexp(z, -1)
+            out[b, :, h] = (torch.softmax(z, -1).view(-1, n) @ v).view(W, -1, D).nan_to_num(0.0)
+    if c["op"] == "decode":
+        out, lse = out[:, 0], lse[:, 0]
+    return {"o": out, "lse": lse}
