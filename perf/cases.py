@@ -220,11 +220,11 @@ def _attn_inputs(c, seed):
 
 def _view_tables(c, s):
     """The views as block tables of a fixed capacity (the budget's pages and a
-    few more for the prefix and suffix): physical pages, logical pages, masks,
-    counts."""
+    few more for the prefix and suffix; with tokens, two partial pages for
+    each of up to 162 runs): physical pages, logical pages, masks, counts."""
     B, cap = c["batch"], s["fbt"].shape[1]
     if c["frac"] < 1.0:
-        cap = min(cap, math.ceil(c["frac"] * c["seq"] / PAGE) + 4)
+        cap = min(cap, math.ceil(c["frac"] * c["seq"] / PAGE) + (324 if c.get("tokens") else 4))
     bt, lb, mk = (np.zeros((B, cap), dtype=np.int32) for _ in range(3))
     for b, (p, m) in enumerate(s["views"]):
         bt[b, :len(p)], lb[b, :len(p)], mk[b, :len(p)] = s["fbt"][b][p], p, m
