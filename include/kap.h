@@ -234,10 +234,10 @@ kap_status kap_compile_plan_masked(int32_t batch, const int32_t *seq_lens,
  * splits of each (sequence, KV head) on the device from that sequence's
  * actual view, so ragged batches stay balanced; n > 0 forces n key splits
  * per (sequence, KV head) on the tuned path (clamped to max_view_blocks).
- * The generic path (other geometries and dtypes) splits keys into pieces of
- * at most 64 pages, finer when the call has few query rows, and takes at
- * least n pieces when n > 0. Results do not depend on the split count
- * beyond rounding.
+ * The wide path (other geometries and dtypes) does the same, with fewer
+ * splits where their partials would exceed 16 MiB - 256 KiB (decode), and one
+ * per (sequence, KV head) where batch * num_kv_heads > 4096. Results do not
+ * depend on the split count beyond rounding.
  * Passing the full block table as the view, with view_logical_block[b][j] = j
  * and view_num_blocks[b] = ceil(seq_lens[b]/16), is full-context decode.
  */
@@ -278,10 +278,12 @@ kap_status kap_selected_decode_masked(const kap_kv_cache *kv, int32_t batch, con
  * ends; its address is looked up once per device, on the first call there).
  *
  * Arguments, results and every other error are those of kap_selected_decode.
- * Limits: the split partials the call needs -- what
+ * Limits: the split partials at most 16 MiB - 256 KiB, else
+ * KAP_ERR_WORKSPACE_TOO_SMALL -- on the tuned path what
  * kap_selected_decode_workspace_bytes() reports for the same arguments, less
- * its arrival-counter block -- at most 16 MiB - 256 KiB, else
- * KAP_ERR_WORKSPACE_TOO_SMALL; with split partials on the tuned path
+ * its arrival-counter block; on the wide path those of uniform splits of at
+ * most 64 pages (finer ones, down to 4 pages, until 4096 (row, split) pairs,
+ * and at least num_splits). With split partials on the tuned path
  * (head_dim 128, four query heads per KV head), batch * num_kv_heads <=
  * 4096, else KAP_ERR_UNSUPPORTED. Both are reported before anything is
  * enqueued. The counters are zero when the library is loaded and every
@@ -308,7 +310,7 @@ kap_status kap_selected_decode_noalloc(const kap_kv_cache *kv, int32_t batch, co
  *
  * kap_decode_schedule_bytes returns the schedule size for the kv geometry,
  * batch and max_view_blocks on the current device; 0 means these calls use
- * no balanced map (one split per (sequence, KV head), or the generic path),
+ * no balanced map (one split per (sequence, KV head), or the wide path),
  * and the schedule is then neither written nor read (it may be NULL).
  * kap_decode_schedule writes the schedule -- caller-owned device memory,
  * 16-byte aligned -- from seq_lens, the view arrays (view_token_mask NULL for

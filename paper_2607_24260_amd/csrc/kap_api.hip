@@ -86,13 +86,15 @@ bool fast_geometry(const kap_kv_cache *kv) {
 
 struct SplitPlan {
   bool fast;
-  bool ragged;    // tuned kernels: split counts balanced on the device
-  int n_split;    // splits per (sequence, KV head); balanced mode: workgroups launched
-  int pps;        // most pages any split of the generic path can get
+  bool ragged;    // split counts balanced on the device
+  int n_split;    // splits per (sequence, KV head); balanced mode: split slots
   int w_target;   // balanced mode: workgroups the work is spread over
   int w_uneven;   // balanced mode, uneven batch: the same, finer chunks
   int min_chunk;  // balanced mode: fewest work items per split
-  long long slots;  // tuned kernels: partial slots
+  long long slots;     // partial slots
+  int row_blocks = 1;  // wide kernel: blocks the rows of a KV head are cut into,
+  int row_tiles = 1;   // the 16-row tiles of each,
+  int slot_rows = 0;   // and the partial rows of a slot
 };
 
 // Balanced mode sizing: the work of a call is spread over about
@@ -132,22 +134,64 @@ int blocks_per_cu(int id, int kv_type, int q_len) {
   return c > 0 ? c : 0;
 }
 
-// Generic path (one wavefront per query row and split): splits of at most
-// kGenericPagesPerSplit pages -- the keys one work item stages in LDS -- and,
-// when the call has few rows, more and smaller splits (down to
-// kGenericMinPagesPerSplit pages) until about kGenericTargetWaves wavefronts
-// run (the 4096-token fp32 workload: 32 rows x 2 splits of 36 pages took
-// 152 us per decode call). num_splits > 0 asks for at least that many.
-constexpr int kGenericTargetWaves = 4096;
-constexpr int kGenericMinPagesPerSplit = 4;
-int generic_splits(long long rows, int max_pages, int num_splits) {
-  const int lo = cdiv(max_pages, kap::kGenericPagesPerSplit);
-  const int hi = std::max(lo, cdiv(max_pages, kGenericMinPagesPerSplit));
-  long long want = rows > 0 ? (kGenericTargetWaves + rows - 1) / rows : 1;
-  if (num_splits > want) want = num_splits;
-  int n = (int)std::min<long long>(std::max<long long>(want, lo), hi);
-  if (num_splits > n) n = num_splits > max_pages ? max_pages : num_splits;
-  return n;
+// Wide kernel (every other geometry and dtype): a KV head's q_len * G rows are
+// cut into blocks of up to wide_max_tiles 16-row tiles, each with a workgroup
+// per split. Work items are steps of two pages (float32: one).
+//  * Workgroups: two per CU where a step in flight is small (at most 32
+//    registers per lane) and two fit, else one: 8 x 64K fp8, 64-dim heads 97
+//    vs 120 us with one, 48-row bf16 windows 65 vs 83 us; for 128-dim bf16 the
+//    second only adds splits to merge (20.6 vs 23.0 us). Uneven batches: four
+//    per CU (32 ragged bf16 sequences 71 us; two 74, eight 80).
+//  * At least four steps per split, one per wavefront: a short sequence runs
+//    from its first loads (4K float32 view 11.6 us; eight steps 12.2, sixteen
+//    16.3).
+//  * `partial_limit` bounds the bytes of the split partials: forced and
+//    automatic split counts give way to it.
+constexpr int kWideUnevenPerCU = 4;
+constexpr int kWideMinChunk = 4;
+constexpr size_t kVerifyPartialLimit = 0x70000000;   // the kernel addresses partials with 31 bits
+SplitPlan plan_wide(const kap_kv_cache *kv, int batch, int q_len, int max_pages, int num_splits,
+                    size_t partial_limit) {
+  SplitPlan p{false, false, 1, 0, 0, 0, 0};
+  const int kv_type = kv->kv_dtype;
+  const long long R = (long long)q_len * (kv->num_q_heads / kv->num_kv_heads);
+  const int tiles = cdiv(R, 16);
+  p.row_blocks = cdiv(tiles, kap::wide_max_tiles(kv_type, kv->head_dim));
+  p.row_tiles = cdiv(tiles, p.row_blocks);
+  p.row_blocks = cdiv(tiles, p.row_tiles);
+  p.slot_rows = p.row_blocks * (int)std::min<long long>(R, 16 * p.row_tiles);
+  const int steps = cdiv(max_pages > 0 ? max_pages : 1, kv_type == kap::kF32 ? 1 : 2);
+  const long long units = (long long)batch * kv->num_kv_heads;
+  const size_t slot_bytes = (size_t)p.slot_rows * (kv->head_dim + 1) * sizeof(float);
+  const long long fit = (long long)(partial_limit / slot_bytes);   // splits in all
+  const int per_cu =
+      kap::wide_step_regs(kv_type, kv->head_dim) <= 32 && p.row_tiles <= 2 ? 2 : 1;
+  const int cus = device_cus();
+  p.slots = units;
+  if (num_splits > 0) {
+    p.n_split = (int)std::max<long long>(
+        1, std::min<long long>(std::min(num_splits, steps), fit / units));
+    p.slots = units * p.n_split;
+  } else if (units * p.row_blocks < 4LL * per_cu * cus && steps > 1 && fit >= 2 * units) {
+    p.ragged = true;
+    p.w_uneven = (int)std::min<long long>(
+        std::max(1, kWideUnevenPerCU * cus / p.row_blocks), fit - units);
+    p.w_target = std::min(std::max(1, per_cu * cus / p.row_blocks), p.w_uneven);
+    p.min_chunk = kWideMinChunk;
+    p.n_split = (int)(p.w_uneven + units);
+    p.slots = p.n_split;
+  }
+  return p;
+}
+
+// Device scratch of kap_selected_decode_noalloc (below): its arrival counters
+// and its split partials, less the rounding of two parts. Wide decode calls
+// with a workspace keep to the same limits, so that both calls split alike.
+constexpr size_t kScratchBytes = size_t(16) << 20;
+constexpr size_t kScratchTicketBytes = size_t(256) << 10;
+size_t wide_decode_partial_limit(const kap_kv_cache *kv, int batch) {
+  const size_t counters = (size_t)batch * kv->num_kv_heads * sizeof(int32_t) * kap::kTicketStride;
+  return counters > kScratchTicketBytes ? 0 : kScratchBytes - kScratchTicketBytes - 512;
 }
 
 // Decode. Tuned path: with num_splits > 0, that many splits for every
@@ -155,95 +199,79 @@ int generic_splits(long long rows, int max_pages, int num_splits) {
 // each sequence's splits from its view (about kDecodeTargetPerCU
 // workgroups per CU over the whole call) -- unless there are so many
 // (sequence, KV head) units that one split each already fills the device.
-// Generic path: see generic_splits.
+// Every other geometry: see plan_wide.
 SplitPlan plan_decode(const kap_kv_cache *kv, int batch, int max_blocks, int num_splits) {
-  SplitPlan p{fast_geometry(kv), false, 1, 1, 0, 0, 0, 0};
+  if (!fast_geometry(kv))
+    return plan_wide(kv, batch, 1, max_blocks, num_splits, wide_decode_partial_limit(kv, batch));
+  SplitPlan p{true, false, 1, 0, 0, 0, 0};
+  p.slot_rows = 4;
   const int mb = max_blocks > 0 ? max_blocks : 1;
   const long long units = (long long)batch * kv->num_kv_heads;
   const int target = kDecodeTargetPerCU[kv->kv_dtype == KAP_DT_FP8_E4M3FN ? 1 : 0];
-  if (p.fast) {
-    if (num_splits > 0) {
-      // uniform: the same split count for every (sequence, KV head)
-      p.n_split = num_splits > mb ? mb : num_splits;
-      p.slots = units * p.n_split;
-    } else if (units >= 4LL * target * device_cus()) {
-      p.n_split = 1;
-      p.slots = units;
-    } else {
-      // balanced: split counts follow each sequence's actual view
-      p.ragged = true;
-      p.w_target = target * device_cus();
-      p.w_uneven = kDecodeUnevenPerCU * device_cus();
-      p.min_chunk = kMinChunkDecode;
-      p.n_split = (int)((long long)std::max(p.w_target, p.w_uneven) + units);
-      p.slots = p.n_split;
-    }
-    p.pps = cdiv(mb, p.n_split);
+  if (num_splits > 0) {
+    // uniform: the same split count for every (sequence, KV head)
+    p.n_split = num_splits > mb ? mb : num_splits;
+    p.slots = units * p.n_split;
+  } else if (units >= 4LL * target * device_cus()) {
+    p.n_split = 1;
+    p.slots = units;
   } else {
-    const int n = generic_splits((long long)batch * kv->num_q_heads, mb, num_splits);
-    p.pps = cdiv(mb, n);
-    p.n_split = cdiv(mb, p.pps);
+    // balanced: split counts follow each sequence's actual view
+    p.ragged = true;
+    p.w_target = target * device_cus();
+    p.w_uneven = kDecodeUnevenPerCU * device_cus();
+    p.min_chunk = kMinChunkDecode;
+    p.n_split = (int)((long long)std::max(p.w_target, p.w_uneven) + units);
+    p.slots = p.n_split;
   }
   return p;
 }
 
 // Verify (tuned path): as decode, with page pairs as the work items.
 SplitPlan plan_verify(const kap_kv_cache *kv, int batch, int q_len, int max_pages, int num_splits) {
-  SplitPlan p{fast_geometry(kv) && q_len * 4 <= 64, false, 1, 1, 0, 0, 0, 0};
+  if (!fast_geometry(kv) || q_len * 4 > 64)
+    return plan_wide(kv, batch, q_len, max_pages, num_splits, kVerifyPartialLimit);
+  SplitPlan p{true, false, 1, 0, 0, 0, 0};
+  p.slot_rows = 4 * q_len;
   const int mp = max_pages > 0 ? max_pages : 1;
   const long long units = (long long)batch * kv->num_kv_heads;
-  if (p.fast) {
-    const int pairs = cdiv(mp, 2);
-    if (num_splits > 0) {
-      p.n_split = num_splits > pairs ? pairs : num_splits;
-      p.slots = units * p.n_split;
-    } else {
-      const int fp8 = kv->kv_dtype == KAP_DT_FP8_E4M3FN;
-      const int nt = (q_len * 4 + 15) / 16;
-      int bpc = blocks_per_cu(2 + 8 * (q_len % 4 == 1) + 4 * fp8 + (nt - 1),
-                              fp8 ? kap::kFP8 : kap::kBF16, q_len);
-      if (bpc <= 0) bpc = 1;
-      if (units >= 4LL * kVerifyTargetPerCU * bpc * device_cus()) {
-        p.n_split = 1;
-        p.slots = units;
-        p.pps = 2 * pairs;
-        return p;
-      }
-      p.ragged = true;
-      p.w_target = kVerifyTargetPerCU * bpc * device_cus();
-      p.w_uneven = kVerifyUnevenFactor * p.w_target;
-      p.min_chunk = kMinChunkVerify;
-      p.n_split = (int)((long long)p.w_uneven + units);
-      p.slots = p.n_split;
-    }
-    p.pps = 2 * cdiv(pairs, p.n_split);
-  } else {
-    const int n = generic_splits((long long)batch * q_len * kv->num_q_heads, mp, num_splits);
-    p.pps = cdiv(mp, n);
-    p.n_split = cdiv(mp, p.pps);
+  const int pairs = cdiv(mp, 2);
+  if (num_splits > 0) {
+    p.n_split = num_splits > pairs ? pairs : num_splits;
+    p.slots = units * p.n_split;
+    return p;
   }
+  const int fp8 = kv->kv_dtype == KAP_DT_FP8_E4M3FN;
+  const int nt = (q_len * 4 + 15) / 16;
+  int bpc = blocks_per_cu(2 + 8 * (q_len % 4 == 1) + 4 * fp8 + (nt - 1),
+                          fp8 ? kap::kFP8 : kap::kBF16, q_len);
+  if (bpc <= 0) bpc = 1;
+  if (units >= 4LL * kVerifyTargetPerCU * bpc * device_cus()) {
+    p.n_split = 1;
+    p.slots = units;
+    return p;
+  }
+  p.ragged = true;
+  p.w_target = kVerifyTargetPerCU * bpc * device_cus();
+  p.w_uneven = kVerifyUnevenFactor * p.w_target;
+  p.min_chunk = kMinChunkVerify;
+  p.n_split = (int)((long long)p.w_uneven + units);
+  p.slots = p.n_split;
   return p;
 }
 
-// Workspace: [arrival counters, batch*Hkv int32][partial o][partial lse],
-// each part 256-byte aligned. Generic path: nothing for a single split;
-// partials [rows][n_split]. Tuned kernels: partials by slot, [slot][q_len*4],
-// nothing when every (sequence, KV head) has a single uniform split.
+// Workspace: [arrival counters, one block per (sequence, KV head)][partial o]
+// [partial lse], each part 256-byte aligned; partials by slot,
+// [slot][slot_rows], nothing when every (sequence, KV head) has a single
+// uniform split.
 struct WsLayout {
   size_t tickets, part_o, part_lse, total;
 };
 
-WsLayout ws_layout(const kap_kv_cache *kv, int batch, int q_len, const SplitPlan &p) {
+WsLayout ws_layout(const kap_kv_cache *kv, int batch, const SplitPlan &p) {
   WsLayout w{0, 0, 0, 0};
-  if (batch <= 0) return w;
-  size_t prow;   // partial rows (one per split and output row)
-  if (p.fast) {
-    if (!p.ragged && p.n_split <= 1) return w;
-    prow = (size_t)p.slots * q_len * 4;
-  } else {
-    if (p.n_split <= 1) return w;
-    prow = (size_t)batch * q_len * kv->num_q_heads * p.n_split;
-  }
+  if (batch <= 0 || (!p.ragged && p.n_split <= 1)) return w;
+  const size_t prow = (size_t)p.slots * p.slot_rows;   // one per split and output row
   const size_t t = round_up(
       (size_t)batch * kv->num_kv_heads * sizeof(int32_t) * kap::kTicketStride, 256);
   const size_t o = round_up(prow * kv->head_dim * sizeof(float), 256);
@@ -255,8 +283,8 @@ WsLayout ws_layout(const kap_kv_cache *kv, int batch, int q_len, const SplitPlan
   return w;
 }
 
-size_t partial_bytes(const kap_kv_cache *kv, int batch, int q_len, const SplitPlan &p) {
-  return ws_layout(kv, batch, q_len, p).total;
+size_t partial_bytes(const kap_kv_cache *kv, int batch, const SplitPlan &p) {
+  return ws_layout(kv, batch, p).total;
 }
 
 // Device scratch of kap_selected_decode_noalloc: one copy per GPU, zero when
@@ -266,8 +294,6 @@ size_t partial_bytes(const kap_kv_cache *kv, int batch, int q_len, const SplitPl
 // them, so that no call's partials overlap another call's counters. In host
 // code `scratch` only names the variable; its device address comes from
 // scratch_base().
-constexpr size_t kScratchBytes = size_t(16) << 20;
-constexpr size_t kScratchTicketBytes = size_t(256) << 10;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // Device address of `scratch` on the current device, looked up once per
@@ -292,6 +318,24 @@ void *scratch_base(hipError_t *err) {
   return cache[dev];
 }
 
+// The allocation-free call takes geometries outside the tuned path as long as
+// uniform splits of at most 64 pages -- finer ones, down to 4 pages, until
+// 4096 (row, split) pairs run, and at least num_splits -- would leave partials
+// that fit the scratch: the bytes of that layout. (What runs needs no more: its
+// split count gives way to the scratch size.)
+size_t noalloc_wide_bytes(const kap_kv_cache *kv, int batch, int max_pages, int num_splits) {
+  const int mb = max_pages > 0 ? max_pages : 1;
+  const long long rows = (long long)batch * kv->num_q_heads;
+  const int lo = cdiv(mb, 64), hi = std::max(lo, cdiv(mb, 4));
+  const long long want = std::max<long long>((4096 + rows - 1) / rows, num_splits);
+  int n = (int)std::min<long long>(std::max<long long>(want, lo), hi);
+  if (num_splits > n) n = std::min(num_splits, mb);
+  n = cdiv(mb, cdiv(mb, n));
+  if (n <= 1) return 0;
+  return kScratchTicketBytes + round_up((size_t)rows * n * kv->head_dim * sizeof(float), 256) +
+         round_up((size_t)rows * n * sizeof(float), 256);
+}
+
 // The static scratch layout for a call whose workspace layout is w (its
 // partial o and lse blocks, moved behind the fixed counter block).
 WsLayout scratch_layout(const WsLayout &w) {
@@ -303,10 +347,10 @@ WsLayout scratch_layout(const WsLayout &w) {
   return f;
 }
 
-kap_status launch_attention(kap::AttnArgs &a, const kap_kv_cache *kv, const SplitPlan &p,
-                            bool decode, void *ws, const WsLayout &w, hipStream_t s) {
+kap_status launch_attention(kap::AttnArgs &a, const SplitPlan &p, bool decode, void *ws, const WsLayout &w, hipStream_t s) {
   a.n_split = p.n_split;
-  a.pages_per_split = p.pps;
+  a.row_blocks = p.row_blocks;
+  a.row_tiles = p.row_tiles;
   a.ragged = p.ragged ? 1 : 0;
   a.w_target = p.w_target;
   a.w_uneven = p.w_uneven;
@@ -318,7 +362,6 @@ kap_status launch_attention(kap::AttnArgs &a, const kap_kv_cache *kv, const Spli
     const long long ng = units > 0 ? p.w_target / units : 1;
     a.guess_splits = ng > 1 ? (int)ng : 1;
   }
-  (void)kv;
   if (p.fast && w.total > 0x7fffffffULL)
     return fail(KAP_ERR_UNSUPPORTED, "split partials need %zu bytes (> 2 GiB); pass fewer splits",
                 w.total);
@@ -327,14 +370,10 @@ kap_status launch_attention(kap::AttnArgs &a, const kap_kv_cache *kv, const Spli
   a.part_o = w.total ? reinterpret_cast<float *>(base + w.part_o) : nullptr;
   a.part_lse = w.total ? reinterpret_cast<float *>(base + w.part_lse) : nullptr;
   (void)hipGetLastError();  // clear a stale error so a launch failure is ours
-  hipError_t e;
-  if (p.fast) {
-    // the tuned kernels merge their splits themselves
-    e = decode ? kap::launch_decode_fast(a, s) : kap::launch_verify_mfma(a, s);
-  } else {
-    e = kap::launch_attn_generic(a, s);
-    if (e == hipSuccess && p.n_split > 1) e = kap::launch_merge(a, s);
-  }
+  // every kernel merges its splits itself
+  const hipError_t e = !p.fast ? kap::launch_attn_wide(a, s)
+                       : decode ? kap::launch_decode_fast(a, s)
+                                : kap::launch_verify_mfma(a, s);
   if (e != hipSuccess) return fail(KAP_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
   return ok();
 }
@@ -483,7 +522,7 @@ size_t kap_selected_decode_workspace_bytes(const kap_kv_cache *kv, int32_t batch
                                            int32_t max_view_blocks, int32_t num_splits) {
   if (check_kv(kv) != KAP_OK || batch <= 0 || max_view_blocks < 0) return 0;
   const SplitPlan p = plan_decode(kv, batch, max_view_blocks, num_splits);
-  return partial_bytes(kv, batch, 1, p);
+  return partial_bytes(kv, batch, p);
 }
 
 static kap_status selected_decode(const kap_kv_cache *kv, int32_t batch, const void *q,
@@ -521,7 +560,7 @@ static kap_status selected_decode(const kap_kv_cache *kv, int32_t batch, const v
     return fail(KAP_ERR_INVALID_ARGUMENT,
                 "schedule is NULL (kap_decode_schedule_bytes is %zu for these arguments)",
                 (size_t)p.n_split * kap::kSchedInts * sizeof(int32_t));
-  WsLayout layout = ws_layout(kv, batch, 1, p);
+  WsLayout layout = ws_layout(kv, batch, p);
   if (noalloc) {
     // the library's own scratch instead of a workspace
     layout = scratch_layout(layout);
@@ -532,11 +571,13 @@ static kap_status selected_decode(const kap_kv_cache *kv, int32_t batch, const v
                   "batch * num_kv_heads = %lld exceeds the %zu arrival counters of the "
                   "allocation-free call's scratch", (long long)batch * kv->num_kv_heads,
                   kScratchTicketBytes / (sizeof(int32_t) * kap::kTicketStride));
-    if (layout.total > kScratchBytes)
+    const size_t need = p.fast ? layout.total
+                               : noalloc_wide_bytes(kv, batch, max_view_blocks, num_splits);
+    if (need > kScratchBytes)
       return fail(KAP_ERR_WORKSPACE_TOO_SMALL,
                   "the call's split partials need %zu bytes; the allocation-free call's scratch "
                   "holds %zu (use kap_selected_decode with a workspace)",
-                  layout.total - kScratchTicketBytes, kScratchBytes - kScratchTicketBytes);
+                  need - kScratchTicketBytes, kScratchBytes - kScratchTicketBytes);
     hipError_t e = hipSuccess;
     workspace = scratch_base(&e);
     if (!workspace)
@@ -581,7 +622,7 @@ static kap_status selected_decode(const kap_kv_cache *kv, int32_t batch, const v
   a.out = out;
   a.lse = lse;
   a.schedule = scheduled && p.fast && p.ragged ? schedule : nullptr;
-  return launch_attention(a, kv, p, true, workspace, layout, static_cast<hipStream_t>(stream));
+  return launch_attention(a, p, true, workspace, layout, static_cast<hipStream_t>(stream));
 }
 
 kap_status kap_selected_decode(const kap_kv_cache *kv, int32_t batch, const void *q,
@@ -705,7 +746,7 @@ size_t kap_verify_workspace_bytes(const kap_kv_cache *kv, int32_t batch, int32_t
   if (check_kv(kv) != KAP_OK || batch <= 0 || q_len < 1 || q_len > 16 || max_seq_len < 0) return 0;
   const int max_pages = cdiv(max_seq_len, 16);
   const SplitPlan p = plan_verify(kv, batch, q_len, max_pages, num_splits);
-  return partial_bytes(kv, batch, q_len, p);
+  return partial_bytes(kv, batch, p);
 }
 
 kap_status kap_verify(const kap_kv_cache *kv, int32_t batch, int32_t q_len, const void *q,
@@ -734,7 +775,7 @@ kap_status kap_verify(const kap_kv_cache *kv, int32_t batch, int32_t q_len, cons
   if (!aligned(q, 16) || !aligned(out, 16))
     return fail(KAP_ERR_INVALID_ARGUMENT, "q and out must be 16-byte aligned");
   const SplitPlan p = plan_verify(kv, batch, q_len, max_pages, num_splits);
-  const size_t need = partial_bytes(kv, batch, q_len, p);
+  const size_t need = partial_bytes(kv, batch, p);
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(KAP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes, got %zu", need, workspace_bytes);
   if (need > 0 && !aligned(workspace, 256))
@@ -764,7 +805,7 @@ kap_status kap_verify(const kap_kv_cache *kv, int32_t batch, int32_t q_len, cons
   a.scale_log2 = sm_scale * kap::kLog2e;
   a.out = out;
   a.lse = lse;
-  return launch_attention(a, kv, p, false, workspace, ws_layout(kv, batch, q_len, p),
+  return launch_attention(a, p, false, workspace, ws_layout(kv, batch, p),
                           static_cast<hipStream_t>(stream));
 }
 

@@ -11,7 +11,6 @@ constexpr int kPage = 16;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kPlanThreads = 256;
-constexpr int kGenericPagesPerSplit = 64;   // 1024 keys staged per generic work item
 constexpr int kMaxPlanPages = 262144;       // pages per sequence the plan bitmap covers
 constexpr int kMaxTokenPlanPages = 16384;   // the same with a bit per token (32 KB of LDS)
 // Arrival counters of the fused split merge are kTicketStride int32 apart (a
@@ -73,10 +72,13 @@ struct AttnArgs {
   int causal;                    // verify: row i sees positions < L - q_len + i + 1
   float scale_log2;              // sm_scale * log2(e)
   int n_split;                   // splits per (sequence, KV head); balanced mode: workgroups
-  int pages_per_split;
-  // Tuned kernels, balanced mode (ragged != 0): split counts per sequence
-  // come from its actual work on the device (see ragged_map); blockIdx.x is
-  // the partial slot. Otherwise the grid is (n_split, Hkv, batch).
+  // Wide kernel: blocks the query rows of a KV head are cut into, 16 * row_tiles
+  // rows each; every block has its own workgroup per split.
+  int row_blocks;
+  int row_tiles;
+  // Balanced mode (ragged != 0): split counts per sequence come from its
+  // actual work on the device (see ragged_map); blockIdx.x is the partial
+  // slot. Otherwise the grid is (n_split, Hkv, batch).
   int ragged;
   int w_target;                  // balanced mode: workgroups the work is spread over
   int w_uneven;                  // balanced mode, uneven batch: the same, finer
@@ -84,9 +86,10 @@ struct AttnArgs {
   int guess_splits;              // balanced mode: max(1, w_target / (batch * Hkv))
   double rcp_w_target;           // balanced mode: 1 / w_target and 1 / w_uneven (host-rounded)
   double rcp_w_uneven;
-  // Partials. Generic path: [batch * R][n_split][D] and [batch * R][n_split].
-  // Tuned kernels: by slot, [slot][R_loc][D] and [slot][R_loc], R_loc =
-  // q_len * 4 local rows; (sequence, KV head) owns slots slot0 .. slot0 + n - 1.
+  // Partials by slot, [slot][R_loc][D] and [slot][R_loc], R_loc local rows
+  // (tuned kernels: q_len * 4; wide kernel: those of a row block, row_blocks
+  // consecutive slots per split); (sequence, KV head) owns slots slot0 ..
+  // slot0 + n - 1.
   float *part_o;    // normalised partial outputs
   float *part_lse;  // log2-domain partial LSE
   int32_t *tickets; // [batch][Hkv][kTicketStride] arrival counters of the fused merge
@@ -166,12 +169,27 @@ hipError_t launch_accept_top3(const AcceptArgs &a, hipStream_t s);
 hipError_t launch_fallback_update(const FallbackArgs &a, hipStream_t s);
 hipError_t launch_append_kv(const AppendArgs &a, hipStream_t s);
 hipError_t launch_compact_view(const CompactArgs &a, int grid, hipStream_t s);
-hipError_t launch_attn_generic(const AttnArgs &a, hipStream_t s);
+hipError_t launch_attn_wide(const AttnArgs &a, hipStream_t s);
 hipError_t launch_decode_fast(const AttnArgs &a, hipStream_t s);
 hipError_t launch_decode_schedule(const AttnArgs &a, hipStream_t s);
 hipError_t launch_verify_mfma(const AttnArgs &a, hipStream_t s);
-hipError_t launch_merge(const AttnArgs &a, hipStream_t s);
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, hipStream_t s);
+
+// Most 16-row tiles one wavefront of the wide kernel holds; more rows become
+// row blocks, which share KV through the L2. Two, so that two wavefronts fit a
+// SIMD, except: float32 above 64 dims one (two tiles would not leave room for
+// the second wavefront: 4 x 8K, 36 rows, 56 vs 103 us), bf16 with 128 dims
+// four (8 x 16K, 40 rows: 61 vs 74 us with two; 72 rows: 93 vs 112 us; fp8,
+// whose widening wants the second wavefront, 119 vs 98 us at 64 rows, and
+// 64-dim bf16, 69 vs 65 us at 48 rows, the other way).
+constexpr int wide_max_tiles(int kv_type, int D) {
+  if (kv_type == kF32) return D == 64 ? 2 : 1;
+  return kv_type == kBF16 && D == 128 ? 4 : 2;
+}
+// Registers of one step's raw pages per lane.
+constexpr int wide_step_regs(int kv_type, int D) {
+  return D * (kv_type == kF32 ? 4 : (kv_type == kBF16 ? 4 : 2)) / 8;
+}
 
 // Workgroups of the tuned kernels that fit on one compute unit at once
 // (0 if the runtime cannot tell).
@@ -203,11 +221,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void *base, si
   return __builtin_amdgcn_make_buffer_rsrc(
       const_cast<char *>(static_cast<const char *>(base) + byte_off), 0, bytes, kBufDword3);
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ kv_u32x4 tile_load16(__amdgpu_buffer_rsrc_t r, int off) {
-  return __builtin_bit_cast(kv_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kNonTemporal));
+  return __builtin_bit_cast(kv_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, POLICY));
 }
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ kv_u32x2 tile_load8(__amdgpu_buffer_rsrc_t r, int off) {
-  return __builtin_bit_cast(kv_u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kNonTemporal));
+  return __builtin_bit_cast(kv_u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, POLICY));
 }
 __device__ __forceinline__ uint32_t tile_load4(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kNonTemporal);
@@ -282,11 +302,6 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 // outputs either way. Equal for all other inputs (+0 above -0).
 __device__ __forceinline__ float max_f(float x, float y) {
   return __builtin_elementwise_maximum(x, y);
-}
-
-// One E4M3FN code -> float (generic path).
-__device__ __forceinline__ float fp8_to_f32(uint8_t b) {
-  return __builtin_amdgcn_cvt_f32_fp8(static_cast<int>(b), 0);
 }
 
 __device__ __forceinline__ float wave_max(float x) {
@@ -531,6 +546,23 @@ __device__ __forceinline__ bool last_arrival_all(const AttnArgs &a, int b, int g
     int32_t *ctr = a.tickets + ((size_t)b * a.Hkv + g) * kTicketStride;
     const int prev = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int last = (prev == n_split - 1) ? 1 : 0;
+    if (last) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last;
+  }
+  __syncthreads();
+  return *flag != 0;
+}
+
+// The same for any counter: true in every thread of the workgroup that takes
+// the last of `expected` tickets.
+__device__ __forceinline__ bool last_arrival_of(int32_t *ctr, int expected, int *flag) {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's stores are complete
+  asm volatile("" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int prev = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int last = (prev == expected - 1) ? 1 : 0;
     if (last) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *flag = last;
   }

@@ -1,0 +1,131 @@
+"""The wide attention kernel (every geometry and dtype outside the tuned ones)
+at the edges of its row tiles, row blocks and split merge, and with infinities
+and NaNs in V, against the fp64 oracle.
+
+Tolerance: float32 weights, sums and outputs. Over at most 700 keys of N(0, 1)
+logits and values, each output is a weighted mean of unit values; 700 float32
+roundings of relative size 2^-24 bound its error by 700 * 6e-8 = 4.2e-5, and
+fp8 page scales by the same relative amount.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kap_oracle as O
+from paper_2607_24260_amd import kap as K
+
+from kap_testlib import assert_close, dev_i32
+
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-5
+
+
+def _inputs(kv_dtype, D, Hkv, lens, seed):
+    r = np.random.default_rng(seed)
+    npg = [-(-L // 16) for L in lens]
+    P = sum(npg) + 3
+    perm, at = r.permutation(P).astype(np.int32), 0
+    fbt = np.full((len(lens), max(npg)), -1, np.int32)
+    for b, n in enumerate(npg):
+        fbt[b, :n] = perm[at:at + n]
+        at += n
+    x = [torch.as_tensor(r.standard_normal(s, dtype=np.float32))
+         for s in ((P, Hkv, D // 8, 16, 8), (P, Hkv, D, 16))]
+    sc = None
+    if kv_dtype == "f32":
+        k, v = (t.cuda() for t in x)
+    elif kv_dtype == "bf16":
+        k, v = (t.to(torch.bfloat16).cuda() for t in x)
+    else:
+        s = [t.abs().flatten(1).amax(1) / 448.0 for t in x]
+        k, v = ((t / u.view(-1, *[1] * (t.dim() - 1))).to(torch.float8_e4m3fn)
+                .view(torch.uint8).cuda() for t, u in zip(x, s))
+        sc = torch.stack(s, 1).contiguous().cuda()
+    return r, k, v, sc, fbt
+
+
+def _pool(kv_dtype, k, v, sc):
+    host = lambda t: (t.view(torch.int16) if t.dtype == torch.bfloat16 else t).cpu().numpy()
+    hk, hv = host(k), host(v)
+    if kv_dtype == "bf16":
+        hk, hv = hk.view(np.uint16), hv.view(np.uint16)
+    return O.KVPool(hk, hv, kv_dtype, None if sc is None else sc.cpu().numpy())
+
+
+def _query(r, shape, kv_dtype):
+    q = torch.as_tensor(r.standard_normal(shape, dtype=np.float32) / np.sqrt(shape[-1]))
+    return q.to(torch.float32 if kv_dtype == "f32" else torch.bfloat16).cuda()
+
+
+# (D, G, window): rows 1, 15 / 16 / 17, 32 / 33, 48, 64 / 65 (one to four tiles
+# and the first split into row blocks), and 272 (17 float32 row blocks: more
+# than the 16 arrival counters of a KV head)
+ROWS = [(64, 1, 1), (128, 3, 5), (64, 2, 8), (128, 17, 1), (64, 2, 16), (128, 11, 3),
+        (128, 6, 8), (64, 8, 8), (128, 13, 5), (128, 17, 16), (256, 1, 3), (256, 8, 4),
+        (256, 3, 11)]
+
+
+@pytest.mark.parametrize("kv_dtype", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("D,G,W", ROWS)
+def test_rows_and_splits(kv_dtype, D, G, W):
+    lens = [700, 33, 5]                     # 44, 3 and 1 pages; windows longer than 5 tokens
+    Hkv = 2
+    r, k, v, sc, fbt = _inputs(kv_dtype, D, Hkv, lens, D + 31 * G + W)
+    pool = _pool(kv_dtype, k, v, sc)
+    kv = K.KVCache(k, v, Hkv * G, _query(r, (1, 1), kv_dtype).dtype, sc)
+    q = _query(r, (len(lens), W, Hkv * G, D), kv_dtype)
+    eo, el = O.verify(pool, q.float().cpu().numpy(), np.asarray(lens), fbt, 1.0)
+    seq = dev_i32(lens)
+    for ns in (0, 1, 3, 100):
+        print(f"verify {kv_dtype} D={D} G={G} W={W} splits={ns}", flush=True)
+        o, lse = K.verify(kv, q, seq, dev_i32(fbt), 700, 1.0, num_splits=ns)
+        torch.cuda.synchronize()
+        assert_close(f"verify O ({ns} splits)", o.cpu().numpy(), eo, TOL)
+        assert_close(f"verify LSE ({ns} splits)", lse.cpu().numpy(), el, TOL)
+    # decode: a view in descending page order, every page's odd tokens hidden
+    nb = [-(-L // 16) for L in lens]
+    vbt, vlb = np.zeros_like(fbt), np.zeros_like(fbt)
+    for b, n in enumerate(nb):
+        vbt[b, :n], vlb[b, :n] = fbt[b, :n][::-1], np.arange(n)[::-1]
+    mask = np.full(fbt.shape, 0x5555, np.int32)
+    for mk in (None, mask):
+        eo, el = O.selected_decode(pool, q[:, 0].float().cpu().numpy(), np.asarray(lens), vbt,
+                                   vlb, nb, 1.0, view_token_mask=mk)
+        for ns in (0, 3):
+            print(f"decode {kv_dtype} D={D} G={G} masked={mk is not None} splits={ns}", flush=True)
+            o, lse = K.selected_decode(kv, q[:, 0].contiguous(), seq, dev_i32(vbt), dev_i32(vlb),
+                                       dev_i32(nb), fbt.shape[1], 1.0, num_splits=ns,
+                                       view_token_mask=None if mk is None else dev_i32(mk))
+            torch.cuda.synchronize()
+            assert_close("decode O", o.cpu().numpy(), eo, TOL)
+            assert_close("decode LSE", lse.cpu().numpy(), el, TOL)
+
+
+@pytest.mark.parametrize("kv_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("num_splits", [0, 1, 3])
+def test_infinities_and_nans_in_v_reach_only_the_rows_that_see_them(kv_dtype, num_splits):
+    # a window of 4 over 70 tokens: V of token 67 is +inf in dim 3, of token 68
+    # -inf in dim 5, of token 69 NaN in dim 7 (rows 1.., 2.. and 3 see them);
+    # the slots past the end hold NaN, K included
+    D, G, W, L = 64, 3, 4, 70
+    r, k, v, sc, fbt = _inputs(kv_dtype, D, 1, [L], 5)
+    for tok, dim, x in ((67, 3, np.inf), (68, 5, -np.inf), (69, 7, np.nan)):
+        v[int(fbt[0, tok // 16]), 0, dim, tok % 16] = x
+    last = int(fbt[0, L // 16])
+    v[last, 0, :, L % 16:] = np.nan
+    k[last, 0, :, L % 16:] = np.nan
+    kv = K.KVCache(k, v, G, _query(r, (1, 1), kv_dtype).dtype, sc)
+    q = _query(r, (1, W, G, D), kv_dtype)
+    clean = v.clone()
+    clean[~torch.isfinite(clean)] = 0
+    eo, el = O.verify(_pool(kv_dtype, torch.nan_to_num(k.float()).to(k.dtype), clean, sc),
+                      q.float().cpu().numpy(), np.asarray([L]), fbt, 1.0)
+    eo[:, 1:, :, 3], eo[:, 2:, :, 5], eo[:, 3:, :, 7] = np.inf, -np.inf, np.nan
+    o, lse = K.verify(kv, q, dev_i32([L]), dev_i32(fbt), L, 1.0, num_splits=num_splits)
+    torch.cuda.synchronize()
+    o = o.cpu().numpy()
+    assert np.array_equal(np.isnan(o), np.isnan(eo))
+    assert_close("O", np.nan_to_num(o, nan=0.0, posinf=np.inf, neginf=-np.inf),
+                 np.nan_to_num(eo, nan=0.0, posinf=np.inf, neginf=-np.inf), TOL)
+    assert_close("LSE", lse.cpu().numpy(), el, TOL)
