@@ -9,17 +9,20 @@
 // tiles), copied with 16-byte nontemporal loads and stores.
 #include "kap_internal.h"
 
+#include <type_traits>
+
 namespace kap {
 namespace {
 
 constexpr int kThreads = 256;
 
 // ---------------------------------------------------------------------------
-// append: one workgroup per new token
+// append
 // ---------------------------------------------------------------------------
 
-// Copies elements of type T (the stored KV type). K: element (g, d) of the token goes to
-// [page][g][d / 8][off][d % 8]; V: to [page][g][d][off].
+// One workgroup per token, element by element (type T, the stored KV type):
+// for source arrays that are not 16-byte aligned. K: element (g, d) of the
+// token goes to [page][g][d / 8][off][d % 8]; V: to [page][g][d][off].
 template <typename T>
 __device__ void append_token(const AppendArgs &a, int t, int64_t page, int off) {
   const int Hkv = a.Hkv, D = a.D, C = D / 8;
@@ -50,6 +53,173 @@ __global__ __launch_bounds__(kThreads) void append_kv_kernel(AppendArgs a) {
     append_token<uint16_t>(a, t, page, off);
   else
     append_token<uint8_t>(a, t, page, off);
+}
+
+// Sixteen tokens at a time. A whole page -- 16 consecutive input tokens in the
+// 16 slots of one page, as in the middle of a prefill chunk -- is moved by the
+// workgroups (blockIdx.x) of the 16 tokens it starts in, wherever in them it
+// starts; every other token by the workgroups of its own 16. blockIdx.y names
+// the part of the row: parts 2 p move columns 256 p .. of K, parts 2 p + 1 of
+// V, a column being 4 bytes of a token (4 / ES dims).
+//  * K keeps a token's eight dims of a chunk together: they move as one piece
+//    (8 ES bytes), neighbouring lanes neighbouring tokens.
+//  * V is transposed. A lane reads its column of the 16 tokens; for a whole
+//    page it turns the 16 x 4 bytes around in registers, giving the 64
+//    contiguous bytes of its rows, which go out through LDS so that a store
+//    instruction covers 1 KB; other tokens are stored as single elements.
+// All loads of a workgroup are in flight together: at one token per sequence
+// latency is all there is, at whole pages HBM: 4 x 2048 bf16 tokens, 8 KV heads
+// of 128 dims (67 MB) in 24.9 us per call; one workgroup per token with
+// 2-byte stores 16 and 32 bytes apart took 49 us. (Nontemporal loads: 30 us -- new
+// tokens come from the caches of the kernels that made them.)
+template <int ES>
+__device__ __forceinline__ void transpose_column(const uint32_t x[kPage], uint32_t o[kPage]) {
+  // o: rows of the column's dims, 4 ES dwords each
+  if constexpr (ES == 4) {
+#pragma unroll
+    for (int i = 0; i < kPage; ++i) o[i] = x[i];
+  } else if constexpr (ES == 2) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {          // tokens 2 i, 2 i + 1
+      o[i] = __builtin_amdgcn_perm(x[2 * i + 1], x[2 * i], 0x05040100u);
+      o[8 + i] = __builtin_amdgcn_perm(x[2 * i + 1], x[2 * i], 0x07060302u);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {          // tokens 4 i .. 4 i + 3: a 4 x 4 byte transpose
+      const uint32_t a01 = __builtin_amdgcn_perm(x[4 * i + 1], x[4 * i], 0x05010400u);
+      const uint32_t a23 = __builtin_amdgcn_perm(x[4 * i + 3], x[4 * i + 2], 0x05010400u);
+      const uint32_t b01 = __builtin_amdgcn_perm(x[4 * i + 1], x[4 * i], 0x07030602u);
+      const uint32_t b23 = __builtin_amdgcn_perm(x[4 * i + 3], x[4 * i + 2], 0x07030602u);
+      o[i] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+      o[4 + i] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+      o[8 + i] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+      o[12 + i] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+    }
+  }
+}
+
+template <int ES>
+__global__ __launch_bounds__(kThreads) void append_runs_kernel(AppendArgs a) {
+  typedef uint32_t piece __attribute__((ext_vector_type(ES == 1 ? 2 : 4)));
+  constexpr int kPer = ES == 4 ? 2 : 1;        // pieces of a K chunk
+  constexpr int kColDims = 4 / ES;
+  constexpr int kPartChunks = 32 * kColDims;   // K chunks in 256 columns
+  constexpr int kSteps = kPartChunks / 16;     // 16 chunks x 16 tokens at a time
+  typedef typename std::conditional<
+      ES == 4, uint32_t, typename std::conditional<ES == 2, uint16_t, uint8_t>::type>::type elem;
+  __shared__ kv_u32x4 s_rows[kThreads / 64][256];
+  const int lane = threadIdx.x & 63;
+  const int t0 = blockIdx.x * kPage;
+  const int part = blockIdx.y >> 1;
+  const bool is_v = blockIdx.y & 1;
+  const size_t row = (size_t)a.Hkv * a.D;      // elements of a token
+  const int cols = (int)(row / kColDims);
+
+  // Lane l looks at token t0 - 16 + l: is it in the slot after the token before
+  // it, on the same page; and does its page's first token start 15 such?
+  const int t = t0 - kPage + lane;
+  const int64_t slot = t >= 0 && t < a.num_tokens ? a.slots[t] : -1;
+  const bool good = slot >= 0 && slot < a.num_pages * kPage;
+  const int64_t before = __shfl_up(slot, 1, 64);
+  const int off = (int)(slot & (kPage - 1));
+  const unsigned long long joined =
+      __ballot(lane > 0 && good && before >= 0 && slot == before + 1 && off != 0);
+  const int first = lane - off;                // lane of the page's first token
+  const bool whole = good && first >= 0 && first + 15 < 64 &&
+                     ((joined >> first >> 1) & 0x7FFFu) == 0x7FFFu;
+  const bool mine = lane >= kPage && lane < 2 * kPage;
+  const unsigned long long starts = __ballot(mine && whole && off == 0);   // at most one
+  const unsigned single = (unsigned)(__ballot(mine && good && !whole) >> kPage);
+  if (blockIdx.y == 0 && threadIdx.x < 64 && mine && slot >= 0 && !good && a.bad_slots)
+    atomicAdd(a.bad_slots, 1);
+
+  auto slot_at = [&](int l) {                  // slot of lane l (the same l in every lane)
+    return ((int64_t)__builtin_amdgcn_readlane((int)(slot >> 32), l) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)slot, l);
+  };
+  auto move_k = [&](int token, bool live, int64_t to) {
+    const piece *src = reinterpret_cast<const piece *>(static_cast<const elem *>(a.k_new) +
+                                                       (size_t)token * row);
+    piece *dst = reinterpret_cast<piece *>(static_cast<elem *>(a.k_pages) +
+                                           (size_t)(to / kPage) * row * kPage) +
+                 (to & (kPage - 1)) * kPer;
+    const int c0 = part * kPartChunks + (threadIdx.x >> 4);
+    const int chunks = live ? (int)(row / 8) : 0;
+    piece x[kSteps][kPer];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+      for (int h = 0; h < kPer; ++h)
+        if (c0 + 16 * u < chunks) x[u][h] = src[(c0 + 16 * u) * kPer + h];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+      for (int h = 0; h < kPer; ++h)
+        if (c0 + 16 * u < chunks) dst[(size_t)(c0 + 16 * u) * kPage * kPer + h] = x[u][h];
+  };
+  const int col = part * kThreads + threadIdx.x;
+  auto load_v = [&](int token, unsigned which, uint32_t x[kPage]) {   // tokens token + i, i in which
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(static_cast<const elem *>(a.v_new) +
+                                                             (size_t)token * row) + col;
+#pragma unroll
+    for (int i = 0; i < kPage; ++i)
+      if (col < cols && ((which >> i) & 1u))
+        x[i] = src[(size_t)i * cols];
+  };
+
+  if (starts) {
+    const int f = __builtin_ctzll(starts);     // lane
+    const int64_t to = slot_at(f);
+    const int token = t0 - kPage + f;
+    if (!is_v) {
+      move_k(token + (threadIdx.x & 15), true, to + (threadIdx.x & 15));
+    } else {
+      uint32_t x[kPage] = {}, o[kPage];
+      load_v(token, 0xFFFFu, x);
+      transpose_column<ES>(x, o);
+      // (16-byte units, rotated by column so that the lanes of a write spread
+      // over the banks)
+      kv_u32x4 *buf = s_rows[threadIdx.x >> 6];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        buf[4 * lane + ((i + (lane >> 1)) & 3)] =
+            kv_u32x4{o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]};
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int col0 = part * kThreads + (threadIdx.x & ~63);   // the wavefront's first column
+      kv_u32x4 *dst = reinterpret_cast<kv_u32x4 *>(static_cast<elem *>(a.v_pages) +
+                                                   (size_t)(to / kPage) * row * kPage +
+                                                   (size_t)col0 * kColDims * kPage);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int u = 64 * i + lane, c = u >> 2;
+        if (col0 + c < cols) dst[u] = buf[4 * c + (((u & 3) + (c >> 1)) & 3)];
+      }
+    }
+  }
+  if (single) {
+    if (!is_v) {
+      const int i = threadIdx.x & 15;
+      const int64_t to = ((int64_t)__shfl((int)(slot >> 32), kPage + i, 64) << 32) |
+                         (uint32_t)__shfl((int)slot, kPage + i, 64);
+      const bool live = (single >> i) & 1u;
+      move_k(live ? t0 + i : t0, live, live ? to : 0);
+    } else {
+      uint32_t x[kPage];
+      load_v(t0, single, x);
+#pragma unroll
+      for (int i = 0; i < kPage; ++i)
+        if (col < cols && ((single >> i) & 1u)) {
+          const int64_t to = slot_at(kPage + i);
+          elem *dst = static_cast<elem *>(a.v_pages) + (size_t)(to / kPage) * row * kPage +
+                      (size_t)col * kColDims * kPage + (to & (kPage - 1));
+#pragma unroll
+          for (int e = 0; e < kColDims; ++e) dst[e * kPage] = (elem)(x[i] >> (8 * ES * e));
+        }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -102,7 +272,18 @@ __global__ __launch_bounds__(kThreads) void compact_view_kernel(CompactArgs a) {
 }  // namespace
 
 hipError_t launch_append_kv(const AppendArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(append_kv_kernel, dim3(a.num_tokens), dim3(kThreads), 0, s, a);
+  const auto addr = reinterpret_cast<uintptr_t>(a.k_new) | reinterpret_cast<uintptr_t>(a.v_new);
+  if (addr % 16 != 0) {
+    hipLaunchKernelGGL(append_kv_kernel, dim3(a.num_tokens), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+  }
+  const long long cols = (long long)a.Hkv * a.D * a.elem_bytes / 4;
+  const dim3 grid((a.num_tokens + kPage - 1) / kPage, 2 * (unsigned)((cols + kThreads - 1) / kThreads));
+  switch (a.elem_bytes) {
+    case 4: hipLaunchKernelGGL(append_runs_kernel<4>, grid, dim3(kThreads), 0, s, a); break;
+    case 2: hipLaunchKernelGGL(append_runs_kernel<2>, grid, dim3(kThreads), 0, s, a); break;
+    default: hipLaunchKernelGGL(append_runs_kernel<1>, grid, dim3(kThreads), 0, s, a); break;
+  }
   return hipGetLastError();
 }
 

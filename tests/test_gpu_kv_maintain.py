@@ -165,3 +165,44 @@ def test_compact_view_at_128k_pages_match_source():
         src = vbt[b, :n]
         assert torch.equal(dst.k_pages[b * cap:b * cap + n], kv.k_pages[src])
         assert torch.equal(dst.v_pages[b * cap:b * cap + n], kv.v_pages[src])
+
+
+# slots in stretches: mid-page starts, whole pages, one page twice over in
+# reverse, padding and out-of-pool slots inside a stretch, a last partial run
+def _run_slots(pages):
+    p = [int(x) * 16 for x in np.random.default_rng(9).permutation(pages)]
+    s = [p[0] + i for i in range(11, 16)] + [p[1] + i for i in range(16)]
+    s += [p[2] + i for i in range(16)] + [p[2] + 16 * pages + i for i in range(3)]
+    s += [p[3] + i for i in range(15, -1, -1)]
+    s += [p[4] + i for i in range(7)] + [-1] + [p[4] + i for i in range(8, 16)] + [-5, -4, -1]
+    s += [16 * pages - 1, 16 * pages, 16 * pages + 1] if p[5] != 16 * (pages - 1) else []
+    s += [p[6] + i for i in range(16)] + [p[7] + i for i in range(16)] + [p[8] + i for i in range(1, 14)]
+    out, seen = [], set()
+    for x in s:                                          # no slot of the pool twice
+        if x not in seen or x < 0:
+            out.append(x)
+            seen.add(x)
+    return np.asarray(out, dtype=np.int64)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("Hkv,D,aligned", [(3, 64, True), (8, 128, True), (5, 256, True),
+                                           (2, 128, False)])
+def test_append_runs_bit_exact(dtype, Hkv, D, aligned):
+    kv = small_pool(dtype, num_pages=12, Hkv=Hkv, D=D)
+    before = host_pool(kv, dtype)
+    slots = _run_slots(12)
+    n = len(slots)
+    k_new, v_new = (new_tokens(n, Hkv, D, dtype, s) for s in (2, 3))
+    if not aligned:                                      # one element past a 16-byte boundary
+        k_new, v_new = (torch.cat([x.flatten()[:1], x.flatten()])[1:].view(x.shape)
+                        for x in (k_new, v_new))
+    bad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    K.append_kv(kv, k_new, v_new, torch.as_tensor(slots).cuda(), bad)
+    torch.cuda.synchronize()
+    want, want_bad = O.append_kv(before, to_host_bits(k_new, dtype), to_host_bits(v_new, dtype),
+                                 slots)
+    got = host_pool(kv, dtype)
+    assert int(bad.item()) == want_bad > 0
+    assert np.array_equal(got.k_pages, want.k_pages)
+    assert np.array_equal(got.v_pages, want.v_pages)
