@@ -4,14 +4,13 @@
 // Per sequence the workgroup
 //   1. checks the CSR bounds, the length and the scores (status codes),
 //   2. marks the mandatory prefix / suffix in an LDS bitmap,
-//   3. ranks the spans by (prior desc, start asc, index asc) -- for every
-//      span, 1 to 8 threads (as many as the span count leaves) count how many
-//      spans precede it, and the inverse permutation goes to LDS (to the
-//      workspace when the spans exceed one LDS chunk),
+//   3. ranks the spans by (prior desc, start asc, index asc): a few by counting
+//      for every span how many precede it (1 to 8 threads a span), up to one
+//      LDS chunk by buckets of the prior, more by counting chunk by chunk; the
+//      inverse permutation goes to LDS (to the workspace with several chunks),
 //   4. walks the spans in rank order with one wavefront, 64 at a time: each
 //      lane prices its span against the bitmap (its cost in visible tokens),
-//      a ballot finds the first span that fits, and only a taken span changes
-//      the state -- one round per taken span, not per span,
+//      and every round takes all spans, in order, that surely fit,
 //   5. compacts the bitmap into the ascending logical-page list (staged in
 //      LDS) and maps it through the full block table.
 // Page mode keeps one bit per page; token mode (the visibility mask of
@@ -25,6 +24,15 @@ namespace kap {
 namespace {
 
 constexpr int kRankChunk = 2048;   // ranking keys staged per pass; also the LDS view list
+// Spans ranked by counting all pairs; more are ranked by buckets (187 spans:
+// 12.8 us per call by pairs, 9.0 by buckets; at 118 both took 10.5).
+constexpr int kPairsMost = 128;
+// Most spans in one bucket: a span counts its bucket's spans before it, so
+// one of 512 costs about as much as all pairs among 700 spans.
+constexpr int kBucketMost = 512;
+// Fewest undecided spans worth filtering after a rejection: four batches of
+// the walk (at 128, 288 spans took 16.7 us instead of 14.2).
+constexpr int kFilterLeast = 256;
 
 // The ranking order without the index, as one unsigned integer: the prior,
 // descending (-0 ranks as +0; NaN never gets here), above the start,
@@ -104,8 +112,10 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
   extern __shared__ uint32_t bitmap[];   // page mode: bit per page; token mode: bit per token
   __shared__ int s_flag;
   __shared__ int s_scan[kPlanThreads / 64];
+  __shared__ uint32_t s_minmax[kPlanThreads / 64][4];
   __shared__ long long s_used;
   __shared__ int s_taken;
+  __shared__ int s_next;
   // ranking keys; after the ranking (one chunk) each span's (length, start);
   // at the end the view list (and its token masks)
   __shared__ __align__(16) union {
@@ -116,7 +126,11 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
     } view;
   } s_u;
   uint64_t *const s_key = s_u.key;
-  __shared__ int s_perm[kRankChunk];   // one chunk: rank -> local span index
+  __shared__ uint16_t s_perm[kRankChunk];    // one chunk: rank -> local span index
+  // bucket ranking: counts, then first slots, of two buckets a word; the spans
+  // by bucket
+  __shared__ uint32_t s_cnt[kRankChunk / 2];
+  __shared__ uint16_t s_ord[kRankChunk];
 
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
@@ -155,17 +169,37 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
   const bool one_chunk = n <= kRankChunk;
   if (tid == 0) s_flag = 0;
   __syncthreads();
-  {
-    const int jn4 = (min(n, kRankChunk) + 3) & ~3;
-    const int lim = max(n, jn4);
-    for (int t = tid; t < lim; t += kPlanThreads) {
+  // (one chunk: priors, starts and the lengths that the greedy walk needs are
+  // all loaded before the first is used; the lengths are stored to LDS, beside
+  // the starts, once the ranking is done)
+  constexpr int kSpanRegs = kRankChunk / kPlanThreads;
+  int len_r[kSpanRegs];
+  if (one_chunk) {
+    float pr[kSpanRegs];
+    int st[kSpanRegs];
+#pragma unroll
+    for (int q = 0; q < kSpanRegs; ++q) {
+      if (q * kPlanThreads >= n) break;
+      const int t = min(tid + q * kPlanThreads, n - 1);
+      pr[q] = a.span_prior[lo + t];
+      st[q] = a.span_start[lo + t];
+      len_r[q] = a.span_len[lo + t];
+    }
+#pragma unroll
+    for (int q = 0; q < kSpanRegs; ++q) {
+      if (q * kPlanThreads >= n) break;
+      const int t = tid + q * kPlanThreads;
       if (t < n) {
-        const float pr = a.span_prior[lo + t];
-        if (__builtin_isnan(pr)) s_flag = 1;
-        if (t < kRankChunk) s_key[t] = rank_key(pr, a.span_start[lo + t]);
-      } else {
-        s_key[t] = kPadKey;
+        if (__builtin_isnan(pr[q])) s_flag = 1;
+        s_key[t] = rank_key(pr[q], st[q]);
       }
+    }
+    if (tid < (-n & 3)) s_key[n + tid] = kPadKey;
+  } else {
+    for (int t = tid; t < n; t += kPlanThreads) {
+      const float pr = a.span_prior[lo + t];
+      if (__builtin_isnan(pr)) s_flag = 1;
+      if (t < kRankChunk) s_key[t] = rank_key(pr, a.span_start[lo + t]);
     }
   }
   __syncthreads();
@@ -173,16 +207,6 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
     write_fail(2 /*KAP_PLAN_BAD_SCORE*/, true);
     return;
   }
-  // one chunk: the span lengths the greedy walk needs, loaded now and stored
-  // to LDS (beside the starts) once the ranking is done
-  constexpr int kLenRegs = kRankChunk / kPlanThreads;
-  int len_r[kLenRegs];
-#pragma unroll
-  for (int q = 0; q < kLenRegs; ++q) {
-    const int t = tid + q * kPlanThreads;
-    len_r[q] = (one_chunk && t < n) ? a.span_len[lo + t] : 0;
-  }
-
   // -- mandatory prefix / suffix ----------------------------------------------
   const int pre = min(max(a.prefix[b], 0), L);
   const int suf_start = max(0, L - max(a.suffix[b], 1));
@@ -247,7 +271,110 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
       c_eq += __shfl_xor(c_eq, m);
     }
   };
-  for (int ib = 0; ib < n; ib += kPlanThreads / TS) {
+  bool ranked = false;
+  if (one_chunk && n > kPairsMost) {
+    // Buckets: the high half of the key (the prior), or where it is the same
+    // for all the low half, less its minimum and shifted so that 1024 to 2048
+    // buckets cover its range -- monotone, so a span's rank is its bucket's
+    // first slot plus its rank among the bucket's spans. With more than
+    // kBucketMost spans in one bucket (nearly equal priors) all pairs again.
+    constexpr int kPer = kRankChunk / kPlanThreads;
+    uint64_t ky[kPer];
+    uint32_t lo_h = ~0u, hi_h = 0u, lo_l = ~0u, hi_l = 0u;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = tid + q * kPlanThreads;
+      ky[q] = i < n ? s_key[i] : kPadKey;
+      if (i < n) {
+        const uint32_t h = (uint32_t)(ky[q] >> 32), l = (uint32_t)ky[q];
+        lo_h = min(lo_h, h);
+        hi_h = max(hi_h, h);
+        lo_l = min(lo_l, l);
+        hi_l = max(hi_l, l);
+      }
+    }
+    for (int w = tid; w < kRankChunk / 2; w += kPlanThreads) s_cnt[w] = 0u;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      lo_h = min(lo_h, (uint32_t)__shfl_xor((int)lo_h, o));
+      hi_h = max(hi_h, (uint32_t)__shfl_xor((int)hi_h, o));
+      lo_l = min(lo_l, (uint32_t)__shfl_xor((int)lo_l, o));
+      hi_l = max(hi_l, (uint32_t)__shfl_xor((int)hi_l, o));
+    }
+    if (lane == 0) {
+      uint32_t *m = s_minmax[tid >> 6];
+      m[0] = lo_h; m[1] = hi_h; m[2] = lo_l; m[3] = hi_l;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kPlanThreads / 64; ++w) {
+      lo_h = min(lo_h, s_minmax[w][0]);
+      hi_h = max(hi_h, s_minmax[w][1]);
+      lo_l = min(lo_l, s_minmax[w][2]);
+      hi_l = max(hi_l, s_minmax[w][3]);
+    }
+    const bool by_prior = lo_h != hi_h;
+    const uint32_t base = by_prior ? lo_h : lo_l, range = by_prior ? hi_h - lo_h : hi_l - lo_l;
+    const int shift = range ? max(0, 32 - 11 - __builtin_clz(range)) : 0;
+    int bucket[kPer], place[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = tid + q * kPlanThreads;
+      if (i < n) {
+        bucket[q] = (int)(((by_prior ? (uint32_t)(ky[q] >> 32) : (uint32_t)ky[q]) - base) >> shift);
+        const int at = 16 * (bucket[q] & 1);
+        place[q] = (atomicAdd(&s_cnt[bucket[q] >> 1], 1u << at) >> at) & 0xFFFF;
+      }
+    }
+    __syncthreads();
+    // counts -> first slots, 8 buckets a thread
+    uint32_t c[4];
+    int sum = 0, most = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      c[w] = s_cnt[4 * tid + w];
+      sum += (int)(c[w] & 0xFFFF) + (int)(c[w] >> 16);
+      most = max(most, max((int)(c[w] & 0xFFFF), (int)(c[w] >> 16)));
+    }
+    int all = 0;
+    int at = block_exclusive_scan(sum, s_scan, &all);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int second = at + (int)(c[w] & 0xFFFF);
+      s_cnt[4 * tid + w] = (uint32_t)at | ((uint32_t)second << 16);
+      at = second + (int)(c[w] >> 16);
+    }
+    ranked = !__syncthreads_or(most > kBucketMost);
+    if (ranked) {
+      int b0[kPer];
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kPlanThreads;
+        if (i < n) {
+          b0[q] = (int)(s_cnt[bucket[q] >> 1] >> (16 * (bucket[q] & 1))) & 0xFFFF;
+          s_ord[b0[q] + place[q]] = (uint16_t)i;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kPlanThreads;
+        if (i < n) {
+          const int nx = bucket[q] + 1;
+          const int b1 = nx < kRankChunk ? (int)(s_cnt[nx >> 1] >> (16 * (nx & 1))) & 0xFFFF : n;
+          int rank = b0[q];
+          for (int e = b0[q]; e < b1; ++e) {
+            const int j = s_ord[e];
+            const uint64_t kj = s_key[j];
+            rank += (kj < ky[q]) | ((kj == ky[q]) & (j < i));
+          }
+          s_perm[rank] = (uint16_t)i;
+          if (a.span_selected) a.span_selected[lo + i] = 0;
+        }
+      }
+    }
+  }
+  for (int ib = 0; ib < n && !ranked; ib += kPlanThreads / TS) {
     const int i = ib + tid / TS;
     const bool act = i < n;
     uint64_t ki = kPadKey;
@@ -261,7 +388,7 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
       rank += tied;
     }
     if (act && sub == 0) {
-      if (one_chunk) s_perm[rank] = i;
+      if (one_chunk) s_perm[rank] = (uint16_t)i;
       else a.perm[lo + rank] = i;
       if (a.span_selected) a.span_selected[lo + i] = 0;
     }
@@ -270,7 +397,8 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
   if (one_chunk) {
     // (length, start) of every span for the greedy walk, over its key
 #pragma unroll
-    for (int q = 0; q < kLenRegs; ++q) {
+    for (int q = 0; q < kSpanRegs; ++q) {
+      if (q * kPlanThreads >= n) break;
       const int t = tid + q * kPlanThreads;
       if (t < n) s_key[t] = ((uint64_t)(uint32_t)len_r[q] << 32) | (uint32_t)(s_key[t] & 0xffffffffu);
     }
@@ -299,94 +427,171 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
   // -- greedy selection in rank order (one wavefront) -------------------------
   // The spans are walked 64 ranks at a time, lane l holding the span of rank
   // r0 + l as a bit range [u0, u1) of the bitmap (pages; tokens in token mode)
-  // and its count of bits not yet set. The state changes only when a span is
-  // taken, so every span between two taken ones is decided against the same
-  // state: a ballot finds the first span (in rank order) that fits, the ones
-  // before it are rejected (SKIP) or, if one of them fails, selection ends
-  // (STOP). When span j is taken, each later lane whose range meets j's
-  // subtracts the bits j newly covers (read before j's bits are set), so a
-  // batch costs one round per taken span instead of one per span. Page mode:
-  // every page but the last (always selected) holds 16 tokens, so a span costs
-  // 16 per new page. The budget state is wavefront-uniform.
-  if (tid < 64) {
-    int used = __builtin_amdgcn_readfirstlane((int)s_used);
-    int taken = 0;
-    const int T = a.budget[b];
-    bool stop = false;
-    for (int r0 = 0; r0 < n && !stop; r0 += 64) {
-      int my_i = -1, x = 0, e = 0;
-      if (r0 + lane < n) {
-        // (two separate paths: merged into one load from a selected address,
-        // the LDS and the global read would both become generic loads)
-        int li;
-        if (one_chunk) {
-          li = s_perm[r0 + lane];
-        } else {
-          li = a.perm[lo + r0 + lane];
-          asm volatile("" ::: "memory");
+  // and its cost, 1 (16 in page mode: every page but the last, which is always
+  // selected, holds 16 tokens) per bit not yet set. Taking spans adds to the
+  // used tokens at least what it takes off any other span's cost, so
+  //  * a span that does not fit now never will: it is rejected (SKIP), or
+  //    selection ends there (STOP);
+  //  * the running sum of the costs of the spans that fit bounds what taking
+  //    them in order uses, so all up to the first sum above the budget are
+  //    taken at once, and the bits they newly set are what they cost.
+  // A batch then takes a few rounds, each near the end of the budget smaller,
+  // instead of one round per taken span (4 x 128K, 500 spans, 40% budget, of
+  // which about 190 taken: 101 -> 24 us per call, with the bucket ranking). The budget state is
+  // wavefront-uniform.
+  // Once a span was rejected little of the budget is left: the four wavefronts
+  // then keep, of a long rest of the ranking, only the spans that still fit
+  // (2000 spans: 49 -> 30 us; 475 before all three).
+  const int T = a.budget[b];
+  // bits [u0, u1) of the bitmap span `li` covers; false if it is empty after
+  // clipping to [0, L) (such spans are ignored)
+  auto bit_range = [&](int st32, int len32, int &u0, int &u1) {
+    const long long x64 = st32 > 0 ? st32 : 0;
+    long long e64 = (long long)st32 + (long long)len32;
+    if (e64 > L) e64 = L;
+    const int x = (int)x64, e = (int)(e64 > x64 ? e64 : x64);
+    u0 = TOK ? x : x / kPage;
+    u1 = TOK ? e : (e + kPage - 1) / kPage;
+    return e > x;
+  };
+  int r0 = 0, ranks = n;                  // ranks [r0, ranks) are undecided
+  while (true) {
+    if (tid < 64) {
+      int used = __builtin_amdgcn_readfirstlane((int)s_used);
+      int taken = 0;
+      bool stop = false, rejected = false;
+      for (; r0 < ranks && !stop && !(rejected && one_chunk && ranks - r0 > kFilterLeast); r0 += 64) {
+        int my_i = -1, st32 = 0, len32 = 0;
+        if (r0 + lane < ranks) {
+          // (two separate paths: merged into one load from a selected address,
+          // the LDS and the global read would both become generic loads)
+          int li;
+          if (one_chunk) {
+            li = s_perm[r0 + lane];
+          } else {
+            li = a.perm[lo + r0 + lane];
+            asm volatile("" ::: "memory");
+          }
+          my_i = lo + li;
+          if (one_chunk) {
+            const uint64_t v = s_key[li];
+            st32 = (int)((uint32_t)v ^ 0x80000000u);
+            len32 = (int)(uint32_t)(v >> 32);
+          } else {
+            st32 = a.span_start[my_i];
+            len32 = a.span_len[my_i];
+          }
         }
-        my_i = lo + li;
-        int st32, len32;
-        if (one_chunk) {
-          const uint64_t v = s_key[li];
-          st32 = (int)((uint32_t)v ^ 0x80000000u);
-          len32 = (int)(uint32_t)(v >> 32);
-        } else {
-          st32 = a.span_start[my_i];
-          len32 = a.span_len[my_i];
+        int u0, u1;
+        const bool valid = bit_range(st32, len32, u0, u1);
+        const int words = valid ? ((u1 - 1) >> 5) - (u0 >> 5) + 1 : 0;
+        int fresh = valid ? count_clear<TOK>(bitmap, u0, u1) : 0;
+        bool open = valid;                                // not yet decided
+        bool my_taken = false;
+        while (true) {
+          const int cost = TOK ? fresh : kPage * fresh;
+          const bool fits = open && used + cost <= T;
+          unsigned long long mf = __ballot(fits);
+          if (a.policy == 1 /*KAP_SELECT_STOP*/) {
+            // only the spans before the first that does not fit are left
+            const unsigned long long mx = __ballot(open && !fits);
+            if (mx) {
+              mf &= (mx & -mx) - 1;
+              stop = mf == 0;
+            }
+          } else {
+            rejected |= __ballot(open && !fits) != 0;
+            open = fits;
+          }
+          if (mf == 0) break;
+          // take the fitting spans, in order, up to the first whose sum exceeds
+          // the budget
+          unsigned long long take = mf;
+          if (mf & (mf - 1)) {
+            const int upto = used + wave_scan_add((mf >> lane) & 1 ? cost : 0);
+            const unsigned long long over = mf & __ballot(upto > T);
+            if (over) take = mf & ((over & -over) - 1);
+          }
+          const bool mine = (take >> lane) & 1;
+          taken += __popcll(take);
+          my_taken |= mine;
+          open &= !mine;
+          if ((take & (take - 1)) == 0) {
+            // one span: its cost is exact, and what it newly covers of another
+            // is what is clear in the overlap
+            const int j = __builtin_ctzll(take);
+            const int ju0 = __builtin_amdgcn_readlane(u0, j);
+            const int ju1 = __builtin_amdgcn_readlane(u1, j);
+            used += __builtin_amdgcn_readlane(cost, j);
+            const int c0 = max(u0, ju0), c1 = min(u1, ju1);
+            if (open && c0 < c1) fresh -= count_clear<TOK>(bitmap, c0, c1);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            const int jw1 = (ju1 - 1) >> 5;
+            for (int w = (ju0 >> 5) + lane; w <= jw1; w += 64)
+              atomicOr(&bitmap[w], range_bits(w, ju0, ju1));
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            continue;
+          }
+          // set their bits, counting those that were clear: short spans a lane
+          // each, long ones (up to 64 words at a time) all lanes together
+          constexpr int kOwnWords = TOK ? 2 : 4;
+          int added = 0;
+          if (mine && words <= kOwnWords) {
+            for (int w = u0 >> 5; w <= (u1 - 1) >> 5; ++w) {
+              const uint32_t m = range_bits(w, u0, u1);
+              added += __popc(m & ~atomicOr(&bitmap[w], m));
+            }
+          }
+          unsigned long long wide = __ballot(mine && words > kOwnWords);
+          while (wide) {
+            const int j = __builtin_ctzll(wide);
+            wide &= wide - 1;
+            const int ju0 = __builtin_amdgcn_readlane(u0, j);
+            const int ju1 = __builtin_amdgcn_readlane(u1, j);
+            const int jw1 = (ju1 - 1) >> 5;
+            for (int w = (ju0 >> 5) + lane; w <= jw1; w += 64) {
+              const uint32_t m = range_bits(w, ju0, ju1);
+              added += __popc(m & ~atomicOr(&bitmap[w], m));
+            }
+          }
+          added = lane63(wave_scan_add(added));
+          used += TOK ? added : kPage * added;
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+          if (open) fresh = count_clear<TOK>(bitmap, u0, u1);
         }
-        const long long st = st32;
-        const long long x64 = st > 0 ? st : 0;
-        long long e64 = st + (long long)len32;
-        if (e64 > L) e64 = L;
-        x = (int)x64;
-        e = (int)(e64 > x64 ? e64 : x64);               // e <= x: empty after clipping
+        if (a.span_selected && my_taken) a.span_selected[my_i] = 1;
       }
-      const bool valid = e > x;                         // empty spans are ignored
-      const int u0 = TOK ? x : x / kPage;
-      const int u1 = TOK ? e : (e + kPage - 1) / kPage;
-      int fresh = valid ? count_clear<TOK>(bitmap, u0, u1) : 0;
-      bool my_taken = false;
-      int pos = 0;                                      // lanes below pos are decided
-      while (true) {
-        const int cost = TOK ? fresh : kPage * fresh;
-        const bool open = valid && lane >= pos;
-        const bool fits = used + cost <= T;
-        const unsigned long long mf = __ballot(open && fits);
-        const unsigned long long mx = __ballot(open && !fits);
-        const int j = mf ? __builtin_ctzll(mf) : 64;
-        const int jx = mx ? __builtin_ctzll(mx) : 64;
-        if (a.policy == 1 /*KAP_SELECT_STOP*/ && jx < j) {
-          stop = true;
-          break;
-        }
-        if (j == 64) break;
-        // take span j
-        const int ju0 = __builtin_amdgcn_readlane(u0, j);
-        const int ju1 = __builtin_amdgcn_readlane(u1, j);
-        used += __builtin_amdgcn_readlane(cost, j);
-        ++taken;
-        my_taken |= lane == j;
-        pos = j + 1;
-        const int c0 = max(u0, ju0), c1 = min(u1, ju1);
-        if (valid && lane > j && c0 < c1) fresh -= count_clear<TOK>(bitmap, c0, c1);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        const int jw0 = ju0 >> 5, jw1 = (ju1 - 1) >> 5;
-        for (int wb = jw0; wb <= jw1; wb += 64) {
-          const int w = wb + lane;
-          const bool in = w <= jw1;
-          atomicOr(&bitmap[in ? w : jw1], in ? range_bits(w, ju0, ju1) : 0u);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      if (lane == 0) {
+        s_used = used;
+        s_taken += taken;
+        s_next = stop ? ranks : r0;
       }
-      if (a.span_selected && my_taken) a.span_selected[my_i] = 1;
     }
-    if (lane == 0) {
-      s_used = used;
-      s_taken = taken;
+    __syncthreads();
+    r0 = s_next;
+    if (r0 >= ranks) break;
+    // thread t keeps, of the ranks r0 + 8 t .. + 7, those that fit
+    const int left_to = min(ranks, r0 + 8 * (tid + 1));
+    int keep = 0, at = 0;
+    unsigned which = 0;
+    for (int r = r0 + 8 * tid; r < left_to; ++r) {
+      const uint64_t v = s_key[s_perm[r]];
+      int u0, u1;
+      if (bit_range((int)((uint32_t)v ^ 0x80000000u), (int)(uint32_t)(v >> 32), u0, u1) &&
+          s_used + (TOK ? 1 : kPage) * count_clear<TOK>(bitmap, u0, u1) <= T) {
+        which |= 1u << (r - r0 - 8 * tid);
+        ++keep;
+      }
     }
+    int kept = 0;
+    at = block_exclusive_scan(keep, s_scan, &kept);
+    for (; which; which &= which - 1) s_ord[at++] = s_perm[r0 + 8 * tid + __builtin_ctz(which)];
+    __syncthreads();
+    for (int r = tid; r < kept; r += kPlanThreads) s_perm[r] = s_ord[r];
+    r0 = 0;
+    ranks = kept;
+    __syncthreads();
   }
-  __syncthreads();
 
   // -- compaction: ascending logical pages -> block table ---------------------
   // Token mode: page p is the half p & 1 of token word p >> 1 and is in the
@@ -406,53 +611,63 @@ __global__ __launch_bounds__(kPlanThreads) void compile_plan_kernel(PlanArgs a) 
     write_fail(1 /*KAP_PLAN_OVER_CAPACITY*/, true);
     return;
   }
-  int out = first;
   const int32_t *fbt_row = a.fbt + (size_t)b * a.fbt_stride;
   int32_t *vbt = a.view_bt + (size_t)b * a.capacity;
   int32_t *vlb = a.view_lblk + (size_t)b * a.capacity;
   uint32_t *vmk = TOK ? a.view_mask + (size_t)b * a.capacity : nullptr;
   bool bad = false;
-  // Views of up to kRankChunk pages: the logical pages (and masks) go to LDS
-  // at their output index first, then every thread maps entries k, k + 256,
-  // ... through the full block table, so the table reads are all in flight
-  // at once. Longer views map each page where it is found.
-  const bool staged = nblk <= kRankChunk;
-  auto emit = [&](int p, uint32_t mask) {
-    if (staged) {
-      s_u.view.page[out] = p;
-      if constexpr (TOK) s_u.view.mask[out] = mask;
-    } else {
-      const int page = fbt_row[p];
-      bad |= (page < 0) || ((int64_t)page >= a.num_pages);
-      vlb[out] = p;
-      vbt[out] = page;
-      if constexpr (TOK) vmk[out] = mask;
-    }
-    ++out;
-  };
-  for (int w = w0; w < w1; ++w) {
-    const uint32_t x = bitmap[w];
-    if constexpr (TOK) {
-      if (x & 0xFFFFu) emit(2 * w, x & 0xFFFFu);
-      if (x >> 16) emit(2 * w + 1, x >> 16);
-    } else {
-      uint32_t bits = x;
-      while (bits) {
-        const int bit = __ffs(bits) - 1;
-        bits &= bits - 1u;
-        emit(w * 32 + bit, 0u);
+  // kRankChunk entries at a time, the logical pages (and masks) go to LDS at
+  // their output index, then every thread maps entries k, k + 256, ... through
+  // the full block table, so that the table reads are all in flight at once.
+  for (int k0 = 0; k0 < nblk; k0 += kRankChunk) {
+    if (k0 > 0) __syncthreads();             // the entries before are read
+    int out = first - k0;                    // below 0 or past the chunk: another chunk's
+    auto emit = [&](int p, uint32_t mask) {
+      if (out >= 0 && out < kRankChunk) {
+        s_u.view.page[out] = p;
+        if constexpr (TOK) s_u.view.mask[out] = mask;
+      }
+      ++out;
+    };
+    if (out < kRankChunk && out + mine > 0) {
+      for (int w = w0; w < w1; ++w) {
+        const uint32_t x = bitmap[w];
+        if constexpr (TOK) {
+          if (x & 0xFFFFu) emit(2 * w, x & 0xFFFFu);
+          if (x >> 16) emit(2 * w + 1, x >> 16);
+        } else {
+          uint32_t bits = x;
+          while (bits) {
+            const int bit = __ffs(bits) - 1;
+            bits &= bits - 1u;
+            emit(w * 32 + bit, 0u);
+          }
+        }
       }
     }
-  }
-  if (staged) {
     __syncthreads();
-    for (int k = tid; k < nblk; k += kPlanThreads) {
-      const int p = s_u.view.page[k];
-      const int page = fbt_row[p];
-      bad |= (page < 0) || ((int64_t)page >= a.num_pages);
-      vlb[k] = p;
-      vbt[k] = page;
-      if constexpr (TOK) vmk[k] = s_u.view.mask[k];
+    const int cnt = min(kRankChunk, nblk - k0);
+    constexpr int kPer = kRankChunk / kPlanThreads;
+    int pg[kPer], page[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (q * kPlanThreads >= cnt) break;
+      const int k = tid + q * kPlanThreads;
+      if (k < cnt) {
+        pg[q] = s_u.view.page[k];
+        page[q] = fbt_row[pg[q]];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (q * kPlanThreads >= cnt) break;
+      const int k = tid + q * kPlanThreads;
+      if (k < cnt) {
+        bad |= (page[q] < 0) || ((int64_t)page[q] >= a.num_pages);
+        vlb[k0 + k] = pg[q];
+        vbt[k0 + k] = page[q];
+        if constexpr (TOK) vmk[k0 + k] = s_u.view.mask[k];
+      }
     }
   }
   if (bad) s_flag = 1;

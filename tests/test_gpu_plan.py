@@ -212,3 +212,44 @@ def test_largest_supported_stride(policy):
         _, plans = run_both([L], fbt, [spans], [1000], [300], [budget], policy=policy)
         assert plans[0].status == O.PLAN_OK
     assert plans[0].num_blocks > 2048
+
+
+def ranked_spans(n, kind, L, rng, longest=1024):
+    """n spans whose priors spread over many ranking buckets ("spread"), share
+    a few values ("levels": more than 512 spans in a bucket from about 1600 on)
+    or are all equal ("same": ranked by start, some of them shared)."""
+    prior = {"spread": rng.random(n) ** 8, "levels": rng.choice([-1.0, 0.25, 3.0], n),
+             "same": np.zeros(n)}[kind].astype(np.float32)
+    start = rng.integers(-20, L, n)
+    start[::5] = start[0]
+    return [(int(s), int(k), float(p)) for s, k, p in
+            zip(start, rng.integers(0, longest, n), prior)]
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("kind", ["spread", "levels", "same"])
+@pytest.mark.parametrize("n", [63, 65, 128, 129, 321, 2047, 2048, 2049])
+def test_rankings_and_late_fits(n, kind, policy):
+    # the ranking by pairs (128 spans and fewer), by buckets (up to 2048) and
+    # in chunks; after the first rejection more than 256 undecided spans are
+    # filtered, and a few short ones late in the ranking still fit
+    rng = np.random.default_rng(n + 7 * len(kind))
+    lens = [70000, 9001]
+    spans = [ranked_spans(n, kind, L, rng) for L in lens]
+    spans[0] += [(int(s), 16, -5.0) for s in rng.integers(0, 70000, 40)]
+    fbt = np.stack([rng.permutation(4400 * 2)[:4400] for _ in lens])
+    run_both(lens, fbt, spans, [100, 0], [50, 1], [9000, 700], policy=policy, num_pages=8800)
+
+
+@pytest.mark.parametrize("frac", [0.5, 0.54, 1.0])
+def test_views_longer_than_a_staging_chunk(frac):
+    # 65552 tokens, 4097 pages: views of 2048 pages (frac 0.5), of a little
+    # more, and of two full staging chunks and one page
+    rng = np.random.default_rng(3)
+    L = 65552
+    spans = ranked_spans(400, "spread", L, rng) + [(0, L, -1.0)]
+    budget = int(frac * L) // 16 * 16
+    _, p = run_both([L], [rng.permutation(4097)], [spans], [0], [1], [budget])
+    if frac != 0.54:
+        return
+    assert 2048 < p[0].num_blocks < 4097

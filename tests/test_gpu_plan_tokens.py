@@ -248,3 +248,18 @@ def test_empty_masks_see_no_key():
                                w.max_pages_per_seq, w.sm_scale, view_token_mask=zero)
     torch.cuda.synchronize()
     assert bool((o == 0).all()) and bool(torch.isinf(lse).all()) and bool((lse < 0).all())
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("n,longest", [(129, 1024), (700, 40), (2048, 1024), (150, 60000)])
+def test_rankings_and_late_fits(n, longest, policy):
+    # bucket ranking, the filter after the first rejection, spans of one or two
+    # bitmap words (set by a lane each), of up to 33 and of up to 1875 (set by
+    # all lanes together)
+    from test_gpu_plan import ranked_spans
+    rng = np.random.default_rng(n)
+    lens = [65536, 9001]
+    spans = [ranked_spans(n, "spread", L, rng, longest) for L in lens]
+    spans[0] += [(int(s), 3, -5.0) for s in rng.integers(0, 65536, 30)]
+    fbt = np.stack([rng.permutation(4096 * 2)[:4096] for _ in lens])
+    run_both(lens, fbt, spans, [100, 0], [50, 1], [9000, 700], policy=policy, num_pages=8192)
