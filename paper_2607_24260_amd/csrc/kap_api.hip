@@ -1033,6 +1033,7 @@ kap_status kap_accept_top3(int32_t batch, int32_t window, int32_t vocab, const v
   a.vocab = vocab;
   a.top_k = top_k;
   a.f32 = logits_dtype == KAP_DT_F32;
+  a.cus = device_cus();
   a.logits = logits;
   a.drafts = draft_tokens;
   a.accepted = accepted;

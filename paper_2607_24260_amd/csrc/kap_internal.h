@@ -154,9 +154,10 @@ struct FallbackArgs {
 };
 
 // kap_accept_top3 after host validation.
-constexpr int kAcceptChunk = 16384;  // vocabulary tokens per row workgroup
 struct AcceptArgs {
   int batch, window, vocab, top_k, f32;
+  int cus;                       // compute units of the device
+  int chunk_loads;               // set at launch: 16-byte loads of a row per workgroup
   const void *logits;            // [batch][window][vocab]
   const int32_t *drafts;         // [batch][window - 1]
   int32_t *accepted, *carry;     // [batch]

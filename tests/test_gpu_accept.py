@@ -75,3 +75,58 @@ def test_full_vocabulary_repeated_calls():
         torch.cuda.synchronize()
         assert np.array_equal(m.cpu().numpy(), em) and np.array_equal(c.cpu().numpy(), ec)
     assert 0 < em.mean() < 8
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [3, 5, 7, 8, 9, 4099, 70001])
+def test_rows_at_every_alignment(dtype, V):
+    # a row of V tokens starts at any offset from a 16-byte boundary: tokens
+    # before the first and after the last aligned load, rows without one, and
+    # (70001) several workgroups a row; drafts on both sides of every boundary
+    B, Wn = 11, 17
+    logits, host, drafts = make_case(B, Wn, V, dtype, seed=V)
+    edge = np.resize([0, V - 1, min(8, V - 1), V // 2, min(15, V - 1)], (B, Wn - 1))
+    drafts = np.where(np.arange(Wn - 1) % 3 == 0, edge, drafts).astype(np.int32)
+    for k in (1, 3, 2 ** 31 - 1):
+        m, c = K.accept_top3(logits, torch.as_tensor(drafts).cuda(), top_k=k)
+        torch.cuda.synchronize()
+        em, ec = O.accept_top_k(host, drafts, k)
+        assert np.array_equal(m.cpu().numpy(), em) and np.array_equal(c.cpu().numpy(), ec)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_infinite_and_zero_logits(dtype):
+    # rows of -inf (masked vocabularies), a draft at -inf, +inf maxima, and
+    # -0 beside +0 (equal): ranks and first maxima by index alone
+    B, Wn, V = 6, 4, 1003
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randn((B, Wn, V), generator=g, device="cuda")
+    x[0] = float("-inf")
+    x[1, :, 5:] = float("-inf")
+    x[2, :, 600] = x[2, :, 300] = float("inf")
+    x[3] = torch.where(torch.arange(V, device="cuda") % 2 == 0, 0.0, -0.0)
+    x[4] = -x[4].abs()
+    x[4, :, 700:703] = 0.0
+    logits = x.to(dtype)
+    host = logits.float().cpu().numpy().astype(np.float64)
+    drafts = np.asarray([[0, 2, 3], [900, 0, 4], [300, 600, 301], [0, 1, 2], [700, 701, 702],
+                         [9, 8, 7]], dtype=np.int32)
+    for k in (1, 2, 3, 6):
+        m, c = K.accept_top3(logits, torch.as_tensor(drafts).cuda(), top_k=k)
+        torch.cuda.synchronize()
+        em, ec = O.accept_top_k(host, drafts, k)
+        assert np.array_equal(m.cpu().numpy(), em) and np.array_equal(c.cpu().numpy(), ec)
+
+
+def test_counts_past_the_packed_range():
+    # more than a million tokens and top_k as large: windows are finished by a
+    # launch of their own; workspace counters are zero again after both ways
+    logits, host, drafts = make_case(1, 3, 1200007, torch.bfloat16, seed=1)
+    drafts[0, 1] = int(np.argmin(host[0, 1]))
+    ws = torch.zeros(4096, dtype=torch.uint8, device="cuda")
+    for k in (2 ** 30, 3):
+        m, c = K.accept_top3(logits, torch.as_tensor(drafts).cuda(), top_k=k, workspace=ws)
+        torch.cuda.synchronize()
+        em, ec = O.accept_top_k(host, drafts, k)
+        assert np.array_equal(m.cpu().numpy(), em) and np.array_equal(c.cpu().numpy(), ec)
+        assert not ws.any()
