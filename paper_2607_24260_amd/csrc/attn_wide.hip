@@ -71,8 +71,15 @@ __device__ __forceinline__ float xor32_sum(float x) {
 __device__ __forceinline__ uint32_t pack_hi(float lo, float hi) {
   return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
 }
-__device__ __forceinline__ float below_bf16(float x) {   // x less its truncation to bf16, exact
-  return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+
+// x less its truncation to bf16, the lower (HIGH: upper) half of pair: as one
+// dot product where two wavefronts share a SIMD and the vector unit is what
+// they wait for (R = 256 rows, fp8: 87 vs 93 us), otherwise with mask and
+// subtraction, which start earlier.
+template <bool DOT, bool HIGH>
+__device__ __forceinline__ float rest(uint32_t pair, float x) {
+  if constexpr (DOT) return less_bf16<HIGH>(pair, x);
+  else return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u);
 }
 
 constexpr int elem_bytes(int kv) { return kv == kF32 ? 4 : (kv == kBF16 ? 2 : 1); }
@@ -390,7 +397,7 @@ void attn_wide_kernel(AttnArgs a) {
   auto reset = [&] {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      m[nt] = -INFINITY;
+      m[nt] = kNoMax;
       l[nt] = 0.f;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -516,44 +523,66 @@ void attn_wide_kernel(AttnArgs a) {
 
     // ---- online softmax --------------------------------------------------------------
     const bool needs_mask = !all || k + PPS > first_masked;
+    // (the page scales are the same in every lane: their signs are scalar)
+    int signs = 0;
+#pragma unroll
+    for (int x = 0; x < PPS; ++x)
+      signs |= __builtin_amdgcn_readfirstlane(__float_as_int(ksc[x]));
+    const bool scaled = needs_mask || signs < 0;
     float p[NT][4 * PPS];                       // weights x V scale
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      float z[4 * PPS];
+      // Logits z * kz: the sums themselves with the pages' scales, or (masked
+      // pages, negative scales) the scaled and masked logits with 1. Scaling
+      // by kz >= 0 keeps the order, so only the maxima are scaled here, and
+      // the weights' exponents below are one fused multiply-add each.
+      float z[4 * PPS], kz[PPS];
 #pragma unroll
-      for (int x = 0; x < PPS; ++x)
+      for (int x = 0; x < PPS; ++x) {
+        kz[x] = ksc[x];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) z[4 * x + e] = s[x][nt][e] * ksc[x];
-      if (needs_mask) {
+        for (int e = 0; e < 4; ++e) z[4 * x + e] = s[x][nt][e];
+      }
+      if (scaled) {
 #pragma unroll
         for (int x = 0; x < PPS; ++x) {
+          kz[x] = 1.f;
           const int below = a.causal ? lim[nt] - (k + x) * kPage : kPage;
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (!((vis[x] >> (4 * j + e)) & 1u) || 4 * j + e >= below) z[4 * x + e] = -INFINITY;
+          for (int e = 0; e < 4; ++e) {
+            z[4 * x + e] *= ksc[x];
+            if (needs_mask &&
+                (!((vis[x] >> (4 * j + e)) & 1u) || 4 * j + e >= below)) z[4 * x + e] = -INFINITY;
+          }
         }
       }
-      float mx = z[0];
+      float own = -INFINITY;
 #pragma unroll
-      for (int e = 1; e < 4 * PPS; ++e) mx = max_f(mx, z[e]);
-      mx = xor16_max(mx);
-      mx = xor32_max(mx);
-      const float m_new = max_f(m[nt], mx);
-      const float mref = (m_new == -INFINITY) ? 0.f : m_new;
-      if (m_new > m[nt]) {
-        const float alpha = exp2_fast(m[nt] - mref);
-        l[nt] *= alpha;
+      for (int x = 0; x < PPS; ++x) {
+        float my = z[4 * x];
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          if (CAREFUL && alpha == 0.f) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-          else acc[nt][dt] *= alpha;
+        for (int e = 1; e < 4; ++e) my = max_f(my, z[4 * x + e]);
+        own = max_f(own, my * kz[x]);
+      }
+      if (__any(own > m[nt] + kDefer)) {
+        float mx = xor16_max(own);
+        mx = xor32_max(mx);
+        if (mx > m[nt]) {
+          const float alpha = exp2_fast(m[nt] - mx);
+          l[nt] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) {
+            if (CAREFUL && alpha == 0.f) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            else acc[nt][dt] *= alpha;
+          }
+          m[nt] = mx;
         }
       }
-      m[nt] = m_new;
+      const float mref = m[nt];
       float ps = 0.f;
 #pragma unroll
       for (int e = 0; e < 4 * PPS; ++e) {
-        p[nt][e] = exp2_fast(z[e] - mref);
+        p[nt][e] = exp2_fast(fmaf(z[e], kz[e / 4], -mref));
         ps += p[nt][e];
       }
       l[nt] += ps;
@@ -597,16 +626,17 @@ void attn_wide_kernel(AttnArgs a) {
           }
         }
     } else {
+      constexpr bool kDot = wide_waves(D, NT) == 2;
       u32x4 hi[NT], mid[NT], lo[NT], one[CAREFUL ? NT : 1];
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
           const float p0 = p[nt][2 * w], p1 = p[nt][2 * w + 1];
-          const float r0 = below_bf16(p0), r1 = below_bf16(p1);
           hi[nt][w] = pack_hi(p0, p1);
+          const float r0 = rest<kDot, false>(hi[nt][w], p0), r1 = rest<kDot, true>(hi[nt][w], p1);
           mid[nt][w] = pack_hi(r0, r1);
-          lo[nt][w] = pack_hi(below_bf16(r0), below_bf16(r1));
+          lo[nt][w] = pack_hi(rest<kDot, false>(mid[nt][w], r0), rest<kDot, true>(mid[nt][w], r1));
           if constexpr (CAREFUL)
             one[nt][w] = (p0 != 0.f ? 0x3f80u : 0u) | (p1 != 0.f ? 0x3f800000u : 0u);
         }
@@ -786,7 +816,7 @@ void attn_wide_kernel(AttnArgs a) {
         *reinterpret_cast<f32x4 *>(&s_acc[wave][n][dt * 16 + 4 * j]) =
             acc[nt][c * (DC / 16) + dt];
       if (j == 0) {
-        s_m[wave][n] = m[nt];
+        s_m[wave][n] = lt == 0.f ? -INFINITY : m[nt];   // no key seen
         s_l[wave][n] = lt;
       }
       __syncthreads();

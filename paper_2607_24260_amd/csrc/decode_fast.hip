@@ -19,14 +19,14 @@
 //    reads four chunks of its token and each load instruction reads four full
 //    chunk rows (4 x 128 / 256 bytes). Row rotations sum the four dim groups;
 //    lane l then keeps the logit of head dg, token 4 tg + j.
-//  * softmax: page maxima per head over lane bits 0-1 (quad swaps) and 4-5
-//    (permlane16 / permlane32 swaps); running max and sum per head in every
-//    lane that owns that head.
+//  * softmax: a reference and a sum per head in every lane that owns that head;
+//    where the reference moves, page maxima over lane bits 0-1 (quad swaps) and
+//    4-5 (permlane16 / permlane32 swaps).
 //  * o += p V: every block multiplies the four heads' weights of 4 tokens with
 //    the V values of 4 dims; lane l reads V^T rows l and l + 64 (1 KB
 //    contiguous per load instruction for fp8) and accumulates o for the four
 //    heads at dims l and l + 64. The weights travel through LDS as bf16
-//    hi + lo parts (error below 2^-15 relative), so the matrix product keeps
+//    hi + lo parts (error below 2^-16 relative), so the matrix product keeps
 //    near-fp32 weights.
 // fp8 KV is widened to bf16 at use (exact); per-page scales fold into the
 // logit scale and the weights. Moving the 4 flop per KV byte off the vector
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
     }
   }
 
-  float m_c = -INFINITY;     // running max (log2 units) of head dg
+  float m_c = kNoMax;        // softmax reference (log2 units) of head dg, see kDefer
   float l_c = 0.f;           // partial sum of p over this lane's tokens, head dg
   f32x4 o_lo = {0.f, 0.f, 0.f, 0.f};   // o[head i][dim lane]
   f32x4 o_hi = {0.f, 0.f, 0.f, 0.f};   // o[head i][dim lane + 64]
@@ -369,13 +369,13 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
     s = ((vis >> t) & 1u) ? s * ksc : -INFINITY;
 
     // ---- online softmax ------------------------------------------------------
-    float pm = max_f(s, dpp<kQuadXor1>(s));
-    pm = max_f(pm, dpp<kQuadXor2>(pm));
-    pm = xor16_max(pm);
-    pm = xor32_max(pm);
-    const float m_new = max_f(m_c, pm);
-    if (__any(m_new > m_c)) {
-      const float alpha = exp2_fast(m_c - (m_new == -INFINITY ? 0.f : m_new));
+    if (__any(s > m_c + kDefer)) {
+      float pm = max_f(s, dpp<kQuadXor1>(s));
+      pm = max_f(pm, dpp<kQuadXor2>(pm));
+      pm = xor16_max(pm);
+      pm = xor32_max(pm);
+      const float m_new = max_f(m_c, pm);
+      const float alpha = exp2_fast(m_c - m_new);
       l_c *= alpha;
 #pragma unroll
       for (int hh = 0; hh < 4; ++hh) {
@@ -386,12 +386,12 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
       }
       m_c = m_new;
     }
-    const float p = exp2_fast(s - (m_c == -INFINITY ? 0.f : m_c));
+    const float p = exp2_fast(s - m_c);
     l_c += p;
     const float pv = p * vsc;
     const uint32_t hi = __float_as_uint(pv) & 0xFFFF0000u;
     pw_hi[wave][dg][t] = (uint16_t)(hi >> 16);
-    pw_lo[wave][dg][t] = (uint16_t)(__float_as_uint(pv - __uint_as_float(hi)) >> 16);
+    pw_lo[wave][dg][t] = (uint16_t)round_bf16x2(pv - __uint_as_float(hi), 0.f);
     if (vis != 0xFFFFu) mask_v<KV>(cur, vis);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
   lt = xor16_sum(lt);
   lt = xor32_sum(lt);
   if ((lane & 0x33) == 0) {   // lanes 0, 4, 8, 12: heads 0..3
-    wstat[0][wave][dg] = m_c;
+    wstat[0][wave][dg] = lt == 0.f ? -INFINITY : m_c;   // no key seen
     wstat[1][wave][dg] = lt;
   }
 #pragma unroll

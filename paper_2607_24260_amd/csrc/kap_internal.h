@@ -292,10 +292,42 @@ __device__ __forceinline__ kv_u32x2 fp8x4_to_bf16x4(uint32_t w) {
   return kv_u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
 }
 
+// x less the bf16 value in the lower (HIGH: upper) half of pair, where x is the
+// float that value was truncated from (so the difference is exact): one
+// instruction, in which the other half is multiplied by zero -- it is finite
+// whenever x's row is. The lower half's (-1, 0) comes from a register: the
+// compiler would encode the constant as the inline operand -1.0, which the
+// instruction reads as (0, -1).
+typedef __bf16 kv_bf16_pair __attribute__((ext_vector_type(2)));
+template <bool HIGH>
+__device__ __forceinline__ float less_bf16(uint32_t pair, float x) {
+  uint32_t minus = 0xbf800000u;
+  if constexpr (!HIGH) asm("s_mov_b32 %0, 0xbf80" : "=s"(minus));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(kv_bf16_pair, pair),
+                                         __builtin_bit_cast(kv_bf16_pair, minus), x, false);
+}
+
+// Two floats rounded to nearest bf16, in one instruction.
+__device__ __forceinline__ uint32_t round_bf16x2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, kv_bf16_pair{(__bf16)lo, (__bf16)hi});
+}
+
 // 2^x on the hardware unit, without the range reduction that keeps
 // denormal results: results below 2^-126 may come out as 0. Used for softmax
 // weights, whose sum is at least 1.
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The online softmax of the matrix-core kernels weighs keys against a
+// reference m of their row: the largest logit when it was last moved. It moves
+// (to the row's current maximum, with a rescaling of sum and accumulators) only
+// when some logit exceeds it by more than kDefer: weights then reach up to
+// 2^kDefer, which costs a float nothing, the cross-lane maximum is taken only
+// then, and the accumulators are hardly ever rescaled (before, whenever any of
+// a wavefront's 16 rows met a new maximum: about 16 ln(steps) times). A row
+// that saw no key has m = kNoMax and sum 0: below every logit, and finite, so
+// that masked keys (-inf) weigh 0 against it.
+constexpr float kDefer = 8.f;
+constexpr float kNoMax = -3.402823466e38f;
 
 // max(x, y) as the hardware maximum: unlike fmaxf it does not quiet signalling
 // NaNs first (one instruction per operand whose origin the compiler cannot

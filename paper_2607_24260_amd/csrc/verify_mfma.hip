@@ -21,8 +21,8 @@
 // Lane (j = lane/16, n = lane%16) thus owns query row n of each 16-row tile and
 // keys 4j..4j+3 of both pages, so the online softmax needs only two cross-row
 // steps per page pair. P is split into bf16 hi + lo parts (two PV products):
-// hi = P truncated to bf16, lo = P - hi (exact in fp32) truncated to bf16,
-// which keeps the probability rounding error below 2^-14 relative.
+// hi = P truncated to bf16, lo = P - hi (exact in fp32) rounded to bf16, which
+// keeps the probability rounding error below 2^-16 relative, without bias.
 // The causal mask and the partial last page are handled on the last pages only.
 // When the last row tile holds a single window token (q_len = 4 t + 1), its
 // softmax runs on that token's 4 rows gathered into all 64 lanes rather than
@@ -325,7 +325,7 @@ void verify_mfma_kernel(AttnArgs a) {
   f32x4 acc[NT][8];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    m[nt] = -INFINITY;
+    m[nt] = kNoMax;
     l[nt] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -438,29 +438,29 @@ void verify_mfma_kernel(AttnArgs a) {
             if (!ok || pos >= lim_c4) z0 = -INFINITY;
             if (!ok || pos + 1 >= lim_c4) z1 = -INFINITY;
           }
-          float mx = max_f(z0, z1);
-          mx = max_f(mx, dpp_all<kRowRor(4)>(mx));
-          mx = max_f(mx, dpp_all<kRowRor(8)>(mx));
-          mx = xor16_max(mx);
-          mx = xor32_max(mx);
-          // every lane now holds the running state of row lane % 4, which
-          // for the accumulator lanes (j, n < 4) is their own row
-          const float m_new = max_f(m[nt], mx);
-          const float mref = (m_new == -INFINITY) ? 0.f : m_new;
-          if (m_new > m[nt]) {
-            const float alpha = exp2_fast(m[nt] - mref);
-            l[nt] *= alpha;
+          const float own = max_f(z0, z1);
+          if (__any(own > m[nt] + kDefer)) {
+            float mx = max_f(own, dpp_all<kRowRor(4)>(own));
+            mx = max_f(mx, dpp_all<kRowRor(8)>(mx));
+            mx = xor16_max(mx);
+            mx = xor32_max(mx);
+            // every lane now holds the maximum of row lane % 4, which for the
+            // accumulator lanes (j, n < 4) is their own row
+            if (mx > m[nt]) {
+              const float alpha = exp2_fast(m[nt] - mx);
+              l[nt] *= alpha;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) acc[nt][dt] *= alpha;
-            m[nt] = m_new;
+              for (int dt = 0; dt < 8; ++dt) acc[nt][dt] *= alpha;
+              m[nt] = mx;
+            }
           }
+          const float mref = m[nt];
           const float p0 = exp2_fast(z0 - mref), p1 = exp2_fast(z1 - mref);
           l[nt] += p0 + p1;
           const float vsc = onB ? vscB : vscA;
           const float pv0 = p0 * vsc, pv1 = p1 * vsc;
-          const float pl0 = pv0 - __uint_as_float(__float_as_uint(pv0) & 0xffff0000u);
-          const float pl1 = pv1 - __uint_as_float(__float_as_uint(pv1) & 0xffff0000u);
-          const uint32_t h = pack_bf16_exact(pv0, pv1), lw = pack_bf16_exact(pl0, pl1);
+          const uint32_t h = pack_bf16_exact(pv0, pv1);
+          const uint32_t lw = round_bf16x2(less_bf16<false>(h, pv0), less_bf16<true>(h, pv1));
           // Back to the P^T operand, with the hi and lo weights side by side
           // so that one product per V tile takes both: column n < 4 (lane
           // (j, n)) gets row n's hi pieces, from lanes 16 j + 4 c + n, c = 0..3;
@@ -487,35 +487,38 @@ void verify_mfma_kernel(AttnArgs a) {
           if (!okB || posB >= lim[nt]) z[4 + e] = -INFINITY;
         }
       }
-      float mx = z[0];
+      float own = z[0];
 #pragma unroll
-      for (int e = 1; e < 8; ++e) mx = max_f(mx, z[e]);
-      mx = xor16_max(mx);
-      mx = xor32_max(mx);
-      const float m_new = max_f(m[nt], mx);
-      const float mref = (m_new == -INFINITY) ? 0.f : m_new;
-      if (m_new > m[nt]) {
-        const float alpha = exp2_fast(m[nt] - mref);
-        l[nt] *= alpha;
+      for (int e = 1; e < 8; ++e) own = max_f(own, z[e]);
+      if (__any(own > m[nt] + kDefer)) {
+        float mx = xor16_max(own);
+        mx = xor32_max(mx);
+        if (mx > m[nt]) {
+          const float alpha = exp2_fast(m[nt] - mx);
+          l[nt] *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) acc[nt][dt] *= alpha;
-        m[nt] = m_new;
+          for (int dt = 0; dt < 8; ++dt) acc[nt][dt] *= alpha;
+          m[nt] = mx;
+        }
       }
+      const float mref = m[nt];
       float ps = 0.f;
-      float pv[8], pl[8];
+      float pv[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float p = exp2_fast(z[e] - mref);
         ps += p;
         pv[e] = p * (e < 4 ? vscA : vscB);
-        pl[e] = pv[e] - __uint_as_float(__float_as_uint(pv[e]) & 0xffff0000u);
       }
       l[nt] += ps;
-      // bf16 pairs are the upper halves of the floats (truncation)
-      phi[nt] = u32x4{pack_bf16_exact(pv[0], pv[1]), pack_bf16_exact(pv[2], pv[3]),
-                      pack_bf16_exact(pv[4], pv[5]), pack_bf16_exact(pv[6], pv[7])};
-      plo[nt] = u32x4{pack_bf16_exact(pl[0], pl[1]), pack_bf16_exact(pl[2], pl[3]),
-                      pack_bf16_exact(pl[4], pl[5]), pack_bf16_exact(pl[6], pl[7])};
+      // hi: the upper halves of the floats (truncation); lo: the rest, rounded
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float p0 = pv[2 * w], p1 = pv[2 * w + 1];
+        const uint32_t h = pack_bf16_exact(p0, p1);
+        phi[nt][w] = h;
+        plo[nt][w] = round_bf16x2(less_bf16<false>(h, p0), less_bf16<true>(h, p1));
+      }
     }
 
     if constexpr (KV == kFP8) {
@@ -610,7 +613,7 @@ void verify_mfma_kernel(AttnArgs a) {
     for (int dt = 0; dt < 8; ++dt)
       *reinterpret_cast<f32x4 *>(&s_acc[wave][n][dt * 16 + 4 * j]) = acc[nt][dt];
     if (j == 0) {
-      s_m[wave][n] = m[nt];
+      s_m[wave][n] = lt == 0.f ? -INFINITY : m[nt];   // no key seen
       s_l[wave][n] = lt;
     }
     __syncthreads();

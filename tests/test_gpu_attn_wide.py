@@ -129,3 +129,44 @@ def test_infinities_and_nans_in_v_reach_only_the_rows_that_see_them(kv_dtype, nu
     assert_close("O", np.nan_to_num(o, nan=0.0, posinf=np.inf, neginf=-np.inf),
                  np.nan_to_num(eo, nan=0.0, posinf=np.inf, neginf=-np.inf), TOL)
     assert_close("LSE", lse.cpu().numpy(), el, TOL)
+
+
+@pytest.mark.parametrize("kv_dtype,D,G", [("bf16", 128, 4), ("fp8", 128, 4), ("bf16", 64, 3),
+                                          ("fp8", 256, 4), ("f32", 128, 4)])
+@pytest.mark.parametrize("step", [3.5, -3.5, 7.0])
+def test_logits_that_climb_from_page_to_page(kv_dtype, D, G, step):
+    # every key of page p has the logit step * (p - 30): about 5 or 10 powers of
+    # two between pages, so that the softmax reference stays behind by less
+    # than its allowance or has to move, upwards from -105 or downwards; fp8
+    # page scales carry the value, negative ones included. Weights of the
+    # tuned kernels are rounded to 2^-16 (of values up to about 4: 6e-5), LSEs
+    # of up to 210 to a few 2^-23 of that.
+    L = 44 * 16 - 3
+    r, k, v, sc, fbt = _inputs(kv_dtype, D, 2, [L], 11)
+    k.zero_()
+    val = torch.zeros(k.shape[0], device="cuda")
+    val[torch.as_tensor(fbt[0].astype(np.int64)).cuda()] = \
+        step * (torch.arange(44, device="cuda") - 30).float()
+    if kv_dtype == "fp8":
+        k[:, :, 0, :, 0] = 0x38                                     # 1.0
+        sc[:, 0] = val
+    else:
+        k[:, :, 0, :, 0] = val[:, None, None].to(k.dtype)
+    qd = torch.float32 if kv_dtype == "f32" else torch.bfloat16
+    kv = K.KVCache(k, v, 2 * G, qd, sc)
+    q = torch.zeros((1, 5, 2 * G, D), dtype=qd, device="cuda")
+    q[..., 0] = 1
+    pool = _pool(kv_dtype, k, v, sc)
+    lens, table = np.asarray([L]), dev_i32(np.arange(44)[None])
+    for ns in (0, 1, 4):
+        o, lse = K.verify(kv, q, dev_i32([L]), dev_i32(fbt), L, 1.0, num_splits=ns)
+        od, ld = K.selected_decode(kv, q[:, 0].contiguous(), dev_i32([L]), dev_i32(fbt), table,
+                                   dev_i32([44]), 44, 1.0, num_splits=ns)
+        torch.cuda.synchronize()
+        eo, el = O.verify(pool, q.float().cpu().numpy(), lens, fbt, 1.0)
+        assert_close("verify O", o.cpu().numpy(), eo, 1e-4)
+        assert_close("verify LSE", lse.cpu().numpy(), el, 1e-4)
+        eo, el = O.selected_decode(pool, q[:, 0].float().cpu().numpy(), lens, fbt,
+                                   np.arange(44)[None], [44], 1.0)
+        assert_close("decode O", od.cpu().numpy(), eo, 1e-4)
+        assert_close("decode LSE", ld.cpu().numpy(), el, 1e-4)
