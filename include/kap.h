@@ -69,7 +69,7 @@
  * Token t of logical page j of a sequence is its token 16*j + t; logical page j
  * lives in physical page block_table[j]. Query head h reads KV head
  * h / (num_q_heads / num_kv_heads).
- * Supported: page_size 16; head_dim 128 (64 and 256 on the generic path);
+ * Supported: page_size 16; head_dim 128 (64 and 256 on the wide path);
  * num_q_heads a multiple of num_kv_heads; kv_dtype F32 with q_dtype F32, or
  * kv_dtype BF16 / FP8_E4M3FN with q_dtype BF16.
  *

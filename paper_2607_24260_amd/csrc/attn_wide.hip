@@ -212,11 +212,14 @@ __device__ __forceinline__ u32x2 v_class(u32x2 v, int cls) {
 }
 
 // LSE merge of ns partials (slots slot0, slot0 + stride, ..., of RS rows each)
-// of a row block: rows row0 .. row0 + rows - 1 of (b, g).
-template <int D, int ITEMS>
+// of a row block: rows row0 .. row0 + rows - 1 of (b, g), kBatch splits' loads in
+// flight. float32 calls, whose steps are one page, have the most splits to
+// merge, and sixteen at a time pay there (4K, 5-token window 17.8 vs 18.6 us);
+// elsewhere the registers they take cost more (8 x 16K, 72 bf16 rows 89.8 vs
+// 87.5 us).
+template <int D, int ITEMS, int kBatch>
 __device__ __forceinline__ void merge_wide(const AttnArgs &a, int b, int g, int row0, int rows,
                                            int RS, int slot0, int stride, int ns) {
-  constexpr int kBatch = 8;
   constexpr int D4 = D / 4;
   const auto ro = partial_rsrc(a.part_o);
   const auto rl = partial_rsrc(a.part_lse);
@@ -877,8 +880,9 @@ void attn_wide_kernel(AttnArgs a) {
     if (last_arrival_of(a.tickets + ((size_t)b * a.Hkv + g) * kTicketStride + c,
                         n_split * sharing, &s_flag)) {
       for (int x = c; x < RB; x += kTicketStride)
-        merge_wide<D, (NT > 1 ? 2 : 1)>(a, b, g, x * (16 * NT), min(R - x * (16 * NT), 16 * NT),
-                                        RS, slot0 * RB + x, RB, n_split);
+        merge_wide<D, (NT > 1 ? 2 : 1), (KV == kF32 ? 16 : 8)>(
+            a, b, g, x * (16 * NT), min(R - x * (16 * NT), 16 * NT), RS, slot0 * RB + x, RB,
+            n_split);
     }
   }
 }
