@@ -819,7 +819,9 @@ void attn_wide_kernel(AttnArgs a) {
         *reinterpret_cast<f32x4 *>(&s_acc[wave][n][dt * 16 + 4 * j]) =
             acc[nt][c * (DC / 16) + dt];
       if (j == 0) {
-        s_m[wave][n] = lt == 0.f ? -INFINITY : m[nt];   // no key seen
+        // no key seen; a NaN logit, which never moves the reference and must not
+        // be dropped as a weight of zero against it; or the reference
+        s_m[wave][n] = lt == 0.f ? -INFINITY : (lt != lt ? lt : m[nt]);
         s_l[wave][n] = lt;
       }
       __syncthreads();

@@ -170,3 +170,55 @@ def test_logits_that_climb_from_page_to_page(kv_dtype, D, G, step):
                                    np.arange(44)[None], [44], 1.0)
         assert_close("decode O", od.cpu().numpy(), eo, 1e-4)
         assert_close("decode LSE", ld.cpu().numpy(), el, 1e-4)
+
+
+@pytest.mark.parametrize("kv_dtype,D,G", [("f32", 64, 3), ("bf16", 64, 3), ("fp8", 64, 3),
+                                          ("f32", 128, 4), ("bf16", 128, 2), ("fp8", 256, 5)])
+@pytest.mark.parametrize("where", ["k", "q"])
+@pytest.mark.parametrize("num_splits", [0, 1])
+def test_a_nan_logit_reaches_the_rows_that_see_it(kv_dtype, D, G, where, num_splits):
+    # 700 tokens: with the automatic splits a wavefront has one step, so the
+    # one that meets the NaN has no other logit; with one split it has several.
+    # K: tokens 100 and 698 (seen by the last two rows of the window of 4) of KV
+    # head 0. Q: window token 1 of the last query head.
+    L, W, Hkv = 700, 4, 2
+    r, k, v, sc, fbt = _inputs(kv_dtype, D, Hkv, [L], 17)
+    kv = K.KVCache(k, v, Hkv * G, _query(r, (1, 1), kv_dtype).dtype, sc)
+    q = _query(r, (1, W, Hkv * G, D), kv_dtype)
+    pool = _pool(kv_dtype, k, v, sc)
+    nan = 0x7F if kv_dtype == "fp8" else np.nan
+    for toks in ((698,), (100, 698)) if where == "k" else ((),):
+        eo, el = (x.copy() for x in O.verify(pool, q.float().cpu().numpy(), np.asarray([L]), fbt,
+                                             1.0))
+        kn, qn = k.clone(), q.clone()
+        for tok in toks:
+            kn[int(fbt[0, tok // 16]), 0, 1, tok % 16, 3] = nan
+            first = max(0, tok - (L - W))            # rows first.. see the token
+            eo[:, first:, :G], el[:, first:, :G] = np.nan, np.nan
+        if where == "q":
+            qn[0, 1, -1, 5] = np.nan
+            eo[0, 1, -1], el[0, 1, -1] = np.nan, np.nan
+        kv = K.KVCache(kn, v, Hkv * G, q.dtype, sc)
+        calls = [("verify", K.verify(kv, qn, dev_i32([L]), dev_i32(fbt), L, 1.0,
+                                     num_splits=num_splits), eo, el)]
+        if 100 in toks or where == "q":
+            # decode of the window's last (Q: second) row over the whole context:
+            # the last row sees every key, the second one every key but two
+            i = 1 if where == "q" else W - 1
+            do, dl = (x.copy() for x in O.selected_decode(
+                pool, q[:, i].float().cpu().numpy(), np.asarray([L]), fbt,
+                np.arange(fbt.shape[1])[None], [fbt.shape[1]], 1.0))
+            if where == "q":
+                do[0, -1], dl[0, -1] = np.nan, np.nan
+            else:
+                do[:, :G], dl[:, :G] = np.nan, np.nan
+            calls.append(("decode", K.selected_decode(
+                kv, qn[:, i].contiguous(), dev_i32([L]), dev_i32(fbt),
+                dev_i32(np.arange(fbt.shape[1])[None]), dev_i32([fbt.shape[1]]), fbt.shape[1], 1.0,
+                num_splits=num_splits), do, dl))
+        torch.cuda.synchronize()
+        for name, (o, lse), xo, xl in calls:
+            for part, got, want in (("O", o, xo), ("LSE", lse, xl)):
+                got = got.cpu().numpy()
+                assert np.array_equal(np.isnan(got), np.isnan(want)), f"{name} {part}: NaN rows"
+                assert_close(f"{name} {part}", np.nan_to_num(got), np.nan_to_num(want), TOL)
