@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
   const int d0 = (threadIdx.x & 63) * 2;
   float M = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) M = fmaxf(M, wstat[0][w][hh]);
+  for (int w = 0; w < kWaves; ++w) M = max_f(M, wstat[0][w][hh]);   // NaN included
   const size_t row = (size_t)b * a.Hq + g * 4 + hh;
   float o0 = 0.f, o1v = 0.f, lse2 = -INFINITY;
   if (M != -INFINITY) {

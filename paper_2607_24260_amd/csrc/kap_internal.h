@@ -652,7 +652,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs &a, int b, int g, int 
         float mc = M[it];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j)
-          if (s0 + j < ns) mc = fmaxf(mc, ls[it][j]);
+          if (s0 + j < ns) mc = max_f(mc, ls[it][j]);   // NaN included
         if (mc == -INFINITY) continue;               // every split so far is empty
         const float sc = exp2f(M[it] - mc);          // 0 while M is still -inf
         tot[it] *= sc;

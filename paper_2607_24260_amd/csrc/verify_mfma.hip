@@ -628,7 +628,7 @@ void verify_mfma_kernel(AttnArgs a) {
     if (r < R) {
       float M = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < kVerifyWaves; ++w) M = fmaxf(M, s_m[w][rn]);
+      for (int w = 0; w < kVerifyWaves; ++w) M = max_f(M, s_m[w][rn]);   // NaN included
       if (M != -INFINITY) {
         float den = 0.f;
 #pragma unroll

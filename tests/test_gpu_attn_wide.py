@@ -173,7 +173,8 @@ def test_logits_that_climb_from_page_to_page(kv_dtype, D, G, step):
 
 
 @pytest.mark.parametrize("kv_dtype,D,G", [("f32", 64, 3), ("bf16", 64, 3), ("fp8", 64, 3),
-                                          ("f32", 128, 4), ("bf16", 128, 2), ("fp8", 256, 5)])
+                                          ("f32", 128, 4), ("bf16", 128, 2), ("fp8", 256, 5),
+                                          ("bf16", 128, 4), ("fp8", 128, 4)])
 @pytest.mark.parametrize("where", ["k", "q"])
 @pytest.mark.parametrize("num_splits", [0, 1])
 def test_a_nan_logit_reaches_the_rows_that_see_it(kv_dtype, D, G, where, num_splits):
@@ -217,8 +218,10 @@ def test_a_nan_logit_reaches_the_rows_that_see_it(kv_dtype, D, G, where, num_spl
                 dev_i32(np.arange(fbt.shape[1])[None]), dev_i32([fbt.shape[1]]), fbt.shape[1], 1.0,
                 num_splits=num_splits), do, dl))
         torch.cuda.synchronize()
+        # tuned kernels (128 dims, four heads): weights rounded to 2^-16
+        tol = 1e-4 if (D, G) == (128, 4) and kv_dtype != "f32" else TOL
         for name, (o, lse), xo, xl in calls:
             for part, got, want in (("O", o, xo), ("LSE", lse, xl)):
                 got = got.cpu().numpy()
                 assert np.array_equal(np.isnan(got), np.isnan(want)), f"{name} {part}: NaN rows"
-                assert_close(f"{name} {part}", np.nan_to_num(got), np.nan_to_num(want), TOL)
+                assert_close(f"{name} {part}", np.nan_to_num(got), np.nan_to_num(want), tol)
