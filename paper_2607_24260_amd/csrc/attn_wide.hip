@@ -567,7 +567,7 @@ void attn_wide_kernel(AttnArgs a) {
         for (int e = 1; e < 4; ++e) my = max_f(my, z[4 * x + e]);
         own = max_f(own, my * kz[x]);
       }
-      if (__any(own > m[nt] + kDefer)) {
+      if (__any(own > m[nt] + (CAREFUL ? 0.f : kDefer))) {
         float mx = xor16_max(own);
         mx = xor32_max(mx);
         if (mx > m[nt]) {
@@ -783,17 +783,16 @@ void attn_wide_kernel(AttnArgs a) {
     // product gives 0 * inf = NaN there (hidden tokens' V is cleared above,
     // but rows of a window see different keys, and a weight or one of its
     // parts can be zero on its own). Rather than test V on the way, a
-    // wavefront whose result is not finite walks its share again, keeping
-    // infinities and NaNs of V out of the products and adding them by class
-    // where the weight is not zero.
+    // wavefront whose result is not finite (or large, see kLargeSum) walks its
+    // share again, with weights of at most 1, keeping infinities and NaNs of V
+    // out of the products and adding them by class where the weight is not
+    // zero.
     float t = 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t = fmaf(acc[nt][dt][e], 0.f, t);
-    if (__any(t != 0.f)) {
+      for (int dt = 0; dt < DT; ++dt) t = max_abs(t, acc[nt][dt]);
+    if (__any(!(t < kLargeSum))) {
       reset();
       for (int i = 0; i < n_my; ++i) {
         direct(st[0], i);

@@ -322,6 +322,7 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
   float l_c = 0.f;           // partial sum of p over this lane's tokens, head dg
   f32x4 o_lo = {0.f, 0.f, 0.f, 0.f};   // o[head i][dim lane]
   f32x4 o_hi = {0.f, 0.f, 0.f, 0.f};   // o[head i][dim lane + 64]
+  float defer = kDefer;                // 0 in a second walk, see kLargeSum
 
   const int n_my = u < nb ? div_small(nb - 1 - u, nw) + 1 : 0;
 
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
     s = ((vis >> t) & 1u) ? s * ksc : -INFINITY;
 
     // ---- online softmax ------------------------------------------------------
-    if (__any(s > m_c + kDefer)) {
+    if (__any(s > m_c + defer)) {
       float pm = max_f(s, dpp<kQuadXor1>(s));
       pm = max_f(pm, dpp<kQuadXor2>(pm));
       pm = xor16_max(pm);
@@ -429,29 +430,39 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
   PageRegs<KV> r[RING];
   int pg[RING];
   uint32_t nv[RING];
-  // (each slot's table reads follow its page loads, as in the loop, so the
-  // wait counts at the loop header are the steady-state ones)
-#pragma unroll
-  for (int j = 0; j < RING; ++j) {
-    validate(j < n_my, raw_pg[j], raw_lb[j], raw_mk[j], pg[j], nv[j]);
-    load_page<KV>(r[j], a, pg[j], g, lane, nv[j] != 0u);
-    __builtin_amdgcn_sched_barrier(0);
-    table_issue(u + nw * (j + RING), j);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  const int full = n_my - n_my % RING;
-  for (int i = 0; i < full; i += RING) {
+  for (;;) {
+    // (each slot's table reads follow its page loads, as in the loop, so the
+    // wait counts at the loop header are the steady-state ones)
 #pragma unroll
     for (int j = 0; j < RING; ++j) {
-      process(r[j], pg[j], nv[j]);
-      page_info(i + j + RING < n_my, j, pg[j], nv[j]);
+      validate(j < n_my, raw_pg[j], raw_lb[j], raw_mk[j], pg[j], nv[j]);
       load_page<KV>(r[j], a, pg[j], g, lane, nv[j] != 0u);
-      table_issue(u + nw * (i + j + 2 * RING), j);
+      __builtin_amdgcn_sched_barrier(0);
+      table_issue(u + nw * (j + RING), j);
+      __builtin_amdgcn_sched_barrier(0);
     }
-  }
+    const int full = n_my - n_my % RING;
+    for (int i = 0; i < full; i += RING) {
 #pragma unroll
-  for (int j = 0; j < RING - 1; ++j)
-    if (full + j < n_my) process(r[j], pg[j], nv[j]);
+      for (int j = 0; j < RING; ++j) {
+        process(r[j], pg[j], nv[j]);
+        page_info(i + j + RING < n_my, j, pg[j], nv[j]);
+        load_page<KV>(r[j], a, pg[j], g, lane, nv[j] != 0u);
+        table_issue(u + nw * (i + j + 2 * RING), j);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < RING - 1; ++j)
+      if (full + j < n_my) process(r[j], pg[j], nv[j]);
+    const float t = max_abs(max_abs(0.f, o_lo), o_hi);
+    if (defer == 0.f || !__any(!(t < kLargeSum))) break;
+    defer = 0.f;
+    m_c = kNoMax;
+    l_c = 0.f;
+    o_lo = f32x4{0.f, 0.f, 0.f, 0.f};
+    o_hi = f32x4{0.f, 0.f, 0.f, 0.f};
+    first_entries(wi);
+  }
 
   // ---- per-wave totals -------------------------------------------------------
   float lt = l_c + dpp<kQuadXor1>(l_c);

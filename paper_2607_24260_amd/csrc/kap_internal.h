@@ -247,6 +247,12 @@ __device__ __forceinline__ int opaque_zero() {
   asm volatile("v_mov_b32 %0, 0" : "=v"(z));
   return z;
 }
+// x as a value the compiler cannot trace: nothing derived from it is computed
+// before this point or kept from an earlier one.
+__device__ __forceinline__ int opaque(int x) {
+  asm("" : "+v"(x));
+  return x;
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t table_rsrc(const int32_t *row, int entries) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(row), 0, entries * 4, kBufDword3);
 }
@@ -326,8 +332,16 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 // a wavefront's 16 rows met a new maximum: about 16 ln(steps) times). A row
 // that saw no key has m = kNoMax and sum 0: below every logit, and finite, so
 // that masked keys (-inf) weigh 0 against it.
+//
+// Weights above 1 must not cost range: V of up to the largest float has to
+// come out as it does under weights of at most 1. A wavefront whose
+// accumulators reach kLargeSum in magnitude, or are not finite (an overflow on
+// the way stays visible: infinities never rescale to finite values), walks its
+// share again with a reference that moves at every new maximum. Below
+// kLargeSum the wavefronts of a workgroup can be added up.
 constexpr float kDefer = 8.f;
 constexpr float kNoMax = -3.402823466e38f;
+constexpr float kLargeSum = 0x1p118f;
 
 // max(x, y) as the hardware maximum: unlike fmaxf it does not quiet signalling
 // NaNs first (one instruction per operand whose origin the compiler cannot
@@ -335,6 +349,14 @@ constexpr float kNoMax = -3.402823466e38f;
 // outputs either way. Equal for all other inputs (+0 above -0).
 __device__ __forceinline__ float max_f(float x, float y) {
   return __builtin_elementwise_maximum(x, y);
+}
+
+// The larger magnitude; NaN if either is.
+typedef float kv_f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float max_abs(float m, kv_f32x4 x) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) m = max_f(m, __builtin_fabsf(x[e]));
+  return m;
 }
 
 __device__ __forceinline__ float wave_max(float x) {

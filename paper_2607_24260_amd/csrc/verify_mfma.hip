@@ -291,8 +291,6 @@ void verify_mfma_kernel(AttnArgs a) {
   wi.slot0 = __builtin_amdgcn_readfirstlane(wi.slot0);
   const int split = wi.split, g = wi.g, b = wi.b, n_split = wi.n_split;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int n = lane & 15, j = lane >> 4;
   const int R = a.q_len * 4;
 
   int np_seq = L > 0 ? (int)(((long long)L + kPage - 1) / kPage) : 0;
@@ -304,32 +302,12 @@ void verify_mfma_kernel(AttnArgs a) {
   const int q1 = (int)(((long long)(split + 1) * pairs) / n_split);
   const int32_t *fbt = a.block_table + (size_t)b * a.bt_stride;
 
-  // Q^T operand: row n of each tile, dims 32kb + 8j .. +7
-  u32x4 qop[NT][4];
+  int lane, n, j;                    // set at the start of a walk, as are:
+  u32x4 qop[NT][4];                  // Q^T operand: row n of each tile, dims 32kb + 8j .. +7
   int lim[NT];                       // row sees logical positions < lim
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int r = nt * 16 + n;
-    const int i = r >> 2, hh = r & 3;
-    lim[nt] = (r < R) ? (L - a.q_len + i + 1) : 0;
-    const uint16_t *qp = static_cast<const uint16_t *>(a.q) +
-                         (((size_t)b * a.q_len + (r < R ? i : 0)) * a.Hq + g * 4 + hh) * kD;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      qop[nt][kb] = (r < R) ? *reinterpret_cast<const u32x4 *>(qp + kb * 32 + j * 8)
-                            : u32x4{0u, 0u, 0u, 0u};
-    }
-  }
-
   float m[NT], l[NT];
   f32x4 acc[NT][8];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    m[nt] = kNoMax;
-    l[nt] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  float defer = kDefer;              // 0 in a second walk, see kLargeSum
   const int last_full = (L - a.q_len) / kPage;   // pages below this are fully visible to all rows
   // C4 tile: rows 16 (NT - 1) .. + 3 are the four heads of window token
   // 4 (NT - 1), which sees logical positions below lim_c4
@@ -439,7 +417,7 @@ void verify_mfma_kernel(AttnArgs a) {
             if (!ok || pos + 1 >= lim_c4) z1 = -INFINITY;
           }
           const float own = max_f(z0, z1);
-          if (__any(own > m[nt] + kDefer)) {
+          if (__any(own > m[nt] + defer)) {
             float mx = max_f(own, dpp_all<kRowRor(4)>(own));
             mx = max_f(mx, dpp_all<kRowRor(8)>(mx));
             mx = xor16_max(mx);
@@ -490,7 +468,7 @@ void verify_mfma_kernel(AttnArgs a) {
       float own = z[0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) own = max_f(own, z[e]);
-      if (__any(own > m[nt] + kDefer)) {
+      if (__any(own > m[nt] + defer)) {
         float mx = xor16_max(own);
         mx = xor32_max(mx);
         if (mx > m[nt]) {
@@ -541,9 +519,40 @@ void verify_mfma_kernel(AttnArgs a) {
     if constexpr (KV == kBF16) next_v();
   };
 
+  // A walk begins with the query and zero sums. Everything a lane holds follows
+  // from an opaque lane index, so that no register lives from one walk to the
+  // next (with sums and addresses kept for the second, the three- and four-tile
+  // kernels spilled).
+  auto begin = [&] {
+    lane = opaque(threadIdx.x & 63);
+    n = lane & 15;
+    j = lane >> 4;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int r = nt * 16 + n;
+      const int i = r >> 2, hh = r & 3;
+      lim[nt] = (r < R) ? (L - a.q_len + i + 1) : 0;
+      const uint16_t *qp = static_cast<const uint16_t *>(a.q) +
+                           (((size_t)b * a.q_len + (r < R ? i : 0)) * a.Hq + g * 4 + hh) * kD;
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        qop[nt][kb] = (r < R) ? *reinterpret_cast<const u32x4 *>(qp + kb * 32 + j * 8)
+                              : u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      m[nt] = kNoMax;
+      l[nt] = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
   const int qw = q0 + wave;
   const int n_my = qw < q1 ? (q1 - qw + kVerifyWaves - 1) / kVerifyWaves : 0;
-  if (n_my > 0) {
+  for (;;) {
+    begin();
+    if (n_my == 0) break;
     auto kpair = [&](int i) { return 2 * (qw + kVerifyWaves * min(i, n_my - 1)); };
     // Every round issues all RING loads unconditionally and skips only the
     // processing of pairs past the end: an early exit inside a round would
@@ -591,6 +600,13 @@ void verify_mfma_kernel(AttnArgs a) {
         }
       }
     }
+    float t = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) t = max_abs(t, acc[nt][dt]);
+    if (defer == 0.f || !__any(!(t < kLargeSum))) break;
+    defer = 0.f;
   }
 
   // ---- combine the four wavefronts, tile by tile, then write ----------------------

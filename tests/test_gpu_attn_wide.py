@@ -225,3 +225,45 @@ def test_a_nan_logit_reaches_the_rows_that_see_it(kv_dtype, D, G, where, num_spl
                 got = got.cpu().numpy()
                 assert np.array_equal(np.isnan(got), np.isnan(want)), f"{name} {part}: NaN rows"
                 assert_close(f"{name} {part}", np.nan_to_num(got), np.nan_to_num(want), tol)
+
+
+@pytest.mark.parametrize("kv_dtype,D,G,W", [("bf16", 128, 4, 5), ("bf16", 128, 4, 12),
+                                            ("fp8", 128, 4, 9), ("fp8", 128, 4, 16),
+                                            ("f32", 64, 3, 5), ("bf16", 64, 3, 5),
+                                            ("fp8", 256, 4, 5), ("bf16", 128, 8, 8)])
+@pytest.mark.parametrize("num_splits", [0, 1])
+def test_values_near_the_largest_float(kv_dtype, D, G, W, num_splits):
+    # |V| up to 2^120 under logits that climb by 0.3 (0.43 powers of two) a page:
+    # with weights of at most 1 a wavefront's sums stay below 2^120 * 16 * 2 *
+    # sum(2^(-0.43 k)) < 2^127; with weights of 2^7 against an older reference
+    # they would not. Tolerances relative to 2^120.
+    L, big = 44 * 16, 2.0 ** 120
+    r, k, v, sc, fbt = _inputs(kv_dtype, D, 2, [L], 23)
+    k.zero_()
+    val = torch.zeros(k.shape[0], device="cuda")
+    val[torch.as_tensor(fbt[0].astype(np.int64)).cuda()] = \
+        0.3 * (torch.arange(44, device="cuda") + 1).float()
+    if kv_dtype == "fp8":
+        k[:, :, 0, :, 0] = 0x38                                     # 1.0
+        sc[:, 0] = val
+        sc[:, 1] = big / 448
+    else:
+        k[:, :, 0, :, 0] = val[:, None, None].to(k.dtype)
+        v = (v.float() / v.float().abs().max() * big).to(v.dtype)
+    qd = torch.float32 if kv_dtype == "f32" else torch.bfloat16
+    kv = K.KVCache(k, v, 2 * G, qd, sc)
+    q = torch.zeros((1, W, 2 * G, D), dtype=qd, device="cuda")
+    q[..., 0] = 1
+    pool = _pool(kv_dtype, k, v, sc)
+    lens, table = np.asarray([L]), np.arange(44)[None]
+    print(f"verify, decode {kv_dtype} D={D} G={G} W={W} splits={num_splits}", flush=True)
+    o, lse = K.verify(kv, q, dev_i32([L]), dev_i32(fbt), L, 1.0, num_splits=num_splits)
+    od, ld = K.selected_decode(kv, q[:, 0].contiguous(), dev_i32([L]), dev_i32(fbt),
+                               dev_i32(table), dev_i32([44]), 44, 1.0, num_splits=num_splits)
+    torch.cuda.synchronize()
+    eo, el = O.verify(pool, q.float().cpu().numpy(), lens, fbt, 1.0)
+    assert_close("verify O", o.cpu().numpy() / big, eo / big, 1e-4)
+    assert_close("verify LSE", lse.cpu().numpy(), el, 1e-4)
+    eo, el = O.selected_decode(pool, q[:, 0].float().cpu().numpy(), lens, fbt, table, [44], 1.0)
+    assert_close("decode O", od.cpu().numpy() / big, eo / big, 1e-4)
+    assert_close("decode LSE", ld.cpu().numpy(), el, 1e-4)
