@@ -4,12 +4,14 @@
 
 Each .hip source is compiled to an object in parallel, then linked into
 paper_2607_24260_amd/libkap.so. Every HIP source is compiled with packed
-FP32 instructions disabled.
+FP32 instructions disabled. The build fails when a kernel of a source in
+NO_SPILLS spills vector registers or takes scratch memory.
 """
 from __future__ import annotations
 
 import concurrent.futures as cf
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -29,6 +31,11 @@ HIPCC_FLAGS = [
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
 
+# Sources whose kernels must hold everything in registers: versions of the wide
+# attention kernel that spilled vector registers have returned wrong results.
+NO_SPILLS = {"attn_wide.hip"}
+RESOURCE_REMARKS = "-Rpass-analysis=kernel-resource-usage"
+
 
 def hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
@@ -41,9 +48,27 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
+def spills(remarks: str):
+    """(kernel, spilled vector registers, scratch bytes per lane) of the kernels
+    in the compiler's resource remarks that have either."""
+    found, kernel, scratch = [], None, 0
+    for line in remarks.splitlines():
+        m = re.search(r"(Function Name|ScratchSize \[bytes/lane\]|VGPRs Spill): (\S+)", line)
+        if not m:
+            continue
+        if m[1] == "Function Name":
+            kernel = m[2]
+        elif m[1].startswith("Scratch"):
+            scratch = int(m[2])
+        elif int(m[2]) or scratch:
+            found.append((kernel, int(m[2]), scratch))
+    return found
+
+
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(BUILD, os.path.basename(src)[:-4] + ".o")
-    cmd = [hipcc(), *HIPCC_FLAGS, "-c", src, "-o", obj]
+    checked = os.path.basename(src) in NO_SPILLS
+    cmd = [hipcc(), *HIPCC_FLAGS, *([RESOURCE_REMARKS] if checked else []), "-c", src, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -51,6 +76,12 @@ def _compile(src: str, verbose: bool) -> str:
                      if "packed-fp32-ops" not in l)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{msgs}")
+    if checked:
+        if "VGPRs Spill" not in msgs:
+            raise RuntimeError(f"no resource remarks for {src}: its spills are unknown")
+        if spills(msgs):
+            raise RuntimeError(f"{src} spills (kernel, registers, scratch bytes): {spills(msgs)}")
+        msgs = ""
     if verbose and msgs.strip():
         print(msgs, flush=True)
     return obj

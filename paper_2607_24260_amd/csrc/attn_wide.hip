@@ -412,15 +412,16 @@ void attn_wide_kernel(AttnArgs a) {
 
   // page id and visible tokens of an entry (see decode: an invalid id, or a
   // block past the sequence, has none)
+  // (32-bit scalar arithmetic only: a 64-bit comparison runs on the vector unit,
+  // and a page address built from its result made the compiler loop over the
+  // lanes around every load: 2 x 32K 64-dim bf16, one split 188 vs 167 us, and
+  // the registers of the 256-dim two-tile kernels ran out)
+  const uint32_t page_limit = (uint32_t)(a.num_pages < 0x80000000ll ? a.num_pages : 0x80000000ll);
   auto set_page = [&](PageRegs<KV, D> &r, bool live, int page, int lblk, uint32_t mask) {
-    const long long rem = (long long)L - (long long)lblk * kPage;
-    const int nvalid = (int)(rem < 0 ? 0 : (rem > kPage ? kPage : rem));
-    r.vis = (0xFFFFu >> (kPage - nvalid)) & mask;
-    r.page = page;
-    if (!live || page < 0 || (int64_t)page >= a.num_pages) {
-      r.vis = 0u;
-      r.page = 0;
-    }
+    const int nvalid = lblk < (L >> 4) ? kPage : (lblk == (L >> 4) ? L & (kPage - 1) : 0);
+    const bool ok = live && (uint32_t)page < page_limit;
+    r.vis = ok ? (0xFFFFu >> (kPage - nvalid)) & mask : 0u;
+    r.page = ok ? page : 0;
   };
 
   // One step: pages k .. k + PPS - 1 of the sequence's list. next_k / next_v
@@ -581,6 +582,7 @@ void attn_wide_kernel(AttnArgs a) {
           m[nt] = mx;
         }
       }
+      if constexpr (CAREFUL) asm("" : "+v"(m[nt]));   // one register, not a copy for later
       const float mref = m[nt];
       float ps = 0.f;
 #pragma unroll
