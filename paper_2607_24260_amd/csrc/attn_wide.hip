@@ -329,14 +329,22 @@ void attn_wide_kernel(AttnArgs a) {
     const SeqLoad first = map_first_loads(a, load);
     if (!ragged_map(a, load, first, (int)item, wi, steps_b, L)) return;
   } else {
-    const unsigned u = item / (unsigned)a.n_split;
+    // splits of all (sequence, KV head) pairs in turn: the ones that a short
+    // sequence leaves empty are not all on the same XCDs
+    const unsigned units = (unsigned)a.batch * (unsigned)a.Hkv;
+    const unsigned split_i = item / units, u = item - split_i * units;
     wi.n_split = a.n_split;
-    wi.split = (int)(item - u * a.n_split);
+    wi.split = (int)split_i;
     wi.b = (int)(u / (unsigned)a.Hkv);
     wi.g = (int)(u - (unsigned)wi.b * a.Hkv);
     wi.slot0 = (int)(u * a.n_split);
-    if (wi.b >= a.batch) return;
+    if (wi.split >= a.n_split) return;
     L = a.seq_lens[wi.b];
+    if (a.min_chunk > 0) {
+      const int steps_b = (entries(wi.b, L) + PPS - 1) / PPS;
+      wi.n_split = max(1, min(a.n_split, (steps_b + a.min_chunk - 1) / a.min_chunk));
+      if (wi.split >= wi.n_split) return;
+    }
   }
   // the same in every lane: keep it in scalar registers
   const int split = __builtin_amdgcn_readfirstlane(wi.split);

@@ -90,7 +90,8 @@ struct SplitPlan {
   int n_split;    // splits per (sequence, KV head); balanced mode: split slots
   int w_target;   // balanced mode: workgroups the work is spread over
   int w_uneven;   // balanced mode, uneven batch: the same, finer chunks
-  int min_chunk;  // balanced mode: fewest work items per split
+  int min_chunk;  // balanced mode: fewest work items per split; else (wide kernel,
+                  // if > 0): a sequence has at most one split per so many
   long long slots;     // partial slots
   int row_blocks = 1;  // wide kernel: blocks the rows of a KV head are cut into,
   int row_tiles = 1;   // the 16-row tiles of each,
@@ -145,13 +146,24 @@ int blocks_per_cu(int id, int kv_type, int q_len) {
 //  * At least four steps per split, one per wavefront: a short sequence runs
 //    from its first loads (4K float32 view 11.6 us; eight steps 12.2, sixteen
 //    16.3).
-//  * `partial_limit` bounds the bytes of the split partials: forced and
-//    automatic split counts give way to it.
+//  * The map splits long sequences however many units there are (64 sequences
+//    x 16 heads, float32, one of 32K and 63 of 1K tokens: 268 us, one split per
+//    (sequence, KV head) 1063). Every workgroup computes it over the whole
+//    batch, though, so that with workgroups for four rounds of the device and
+//    more than 64 sequences (a second pass of the map) a sequence is cut by its
+//    own length alone: into pieces of at least kWidePiecePages, as many as make
+//    one of `max_pages` fill the device (256 sequences x 8 heads, 64-dim bf16,
+//    one of 128K and 255 of 256 tokens: 166 us, map 78, one split 686; 300 x 1K
+//    tokens, 4-token windows: 234, map 272, one split 233).
+//  * `partial_limit` bounds the bytes of the split partials of a call that needs
+//    few of them, `partial_most` those of any: split counts give way to them.
 constexpr int kWideUnevenPerCU = 4;
 constexpr int kWideMinChunk = 4;
-constexpr size_t kVerifyPartialLimit = 0x70000000;   // the kernel addresses partials with 31 bits
+constexpr int kWidePiecePages = 256;
+constexpr int kMapPass = 64;                       // sequences per pass of the map
+constexpr size_t kWidePartialLimit = 0x70000000;   // the kernel addresses partials with 31 bits
 SplitPlan plan_wide(const kap_kv_cache *kv, int batch, int q_len, int max_pages, int num_splits,
-                    size_t partial_limit) {
+                    size_t partial_limit, size_t partial_most) {
   SplitPlan p{false, false, 1, 0, 0, 0, 0};
   const int kv_type = kv->kv_dtype;
   const long long R = (long long)q_len * (kv->num_q_heads / kv->num_kv_heads);
@@ -163,16 +175,27 @@ SplitPlan plan_wide(const kap_kv_cache *kv, int batch, int q_len, int max_pages,
   const int steps = cdiv(max_pages > 0 ? max_pages : 1, kv_type == kap::kF32 ? 1 : 2);
   const long long units = (long long)batch * kv->num_kv_heads;
   const size_t slot_bytes = (size_t)p.slot_rows * (kv->head_dim + 1) * sizeof(float);
-  const long long fit = (long long)(partial_limit / slot_bytes);   // splits in all
+  long long fit = (long long)(partial_limit / slot_bytes);   // splits in all
+  const long long fit_most = (long long)(partial_most / slot_bytes);
+  if (fit < 2 * units) fit = fit_most;
   const int per_cu =
       kap::wide_step_regs(kv_type, kv->head_dim) <= 32 && p.row_tiles <= 2 ? 2 : 1;
   const int cus = device_cus();
+  const bool full = units * p.row_blocks >= 4LL * per_cu * cus;   // four rounds of the device
   p.slots = units;
+  const long long most = std::max<long long>(1, std::min<long long>(steps, fit_most / units));
   if (num_splits > 0) {
-    p.n_split = (int)std::max<long long>(
-        1, std::min<long long>(std::min(num_splits, steps), fit / units));
+    p.n_split = (int)std::min<long long>(num_splits, most);
     p.slots = units * p.n_split;
-  } else if (units * p.row_blocks < 4LL * per_cu * cus && steps > 1 && fit >= 2 * units) {
+  } else if (full && max_pages <= 64) {
+    // short sequences: one split each
+  } else if (full && batch > kMapPass) {
+    const int alone = cdiv(cus, (long long)kv->num_kv_heads * p.row_blocks);
+    p.n_split = (int)std::min<long long>(
+        std::min(alone, std::max(1, max_pages / kWidePiecePages)), most);
+    p.min_chunk = cdiv(steps, p.n_split);
+    p.slots = units * p.n_split;
+  } else if (steps > 1 && fit >= 2 * units) {
     p.ragged = true;
     p.w_uneven = (int)std::min<long long>(
         std::max(1, kWideUnevenPerCU * cus / p.row_blocks), fit - units);
@@ -185,13 +208,38 @@ SplitPlan plan_wide(const kap_kv_cache *kv, int batch, int q_len, int max_pages,
 }
 
 // Device scratch of kap_selected_decode_noalloc (below): its arrival counters
-// and its split partials, less the rounding of two parts. Wide decode calls
-// with a workspace keep to the same limits, so that both calls split alike.
+// and its split partials.
 constexpr size_t kScratchBytes = size_t(16) << 20;
 constexpr size_t kScratchTicketBytes = size_t(256) << 10;
-size_t wide_decode_partial_limit(const kap_kv_cache *kv, int batch) {
+
+// The allocation-free call takes geometries outside the tuned path as long as
+// uniform splits of at most 64 pages -- finer ones, down to 4 pages, until
+// 4096 (row, split) pairs run, and at least num_splits -- would leave partials
+// that fit the scratch: the bytes of that layout. (What runs needs no more: its
+// split count gives way to the scratch size.)
+size_t noalloc_wide_bytes(const kap_kv_cache *kv, int batch, int max_pages, int num_splits) {
+  const int mb = max_pages > 0 ? max_pages : 1;
+  const long long rows = (long long)batch * kv->num_q_heads;
+  const int lo = cdiv(mb, 64), hi = std::max(lo, cdiv(mb, 4));
+  const long long want = std::max<long long>((4096 + rows - 1) / rows, num_splits);
+  int n = (int)std::min<long long>(std::max<long long>(want, lo), hi);
+  if (num_splits > n) n = std::min(num_splits, mb);
+  n = cdiv(mb, cdiv(mb, n));
+  if (n <= 1) return 0;
+  return kScratchTicketBytes + round_up((size_t)rows * n * kv->head_dim * sizeof(float), 256) +
+         round_up((size_t)rows * n * sizeof(float), 256);
+}
+
+// Wide decode keeps to that scratch (less the rounding of two parts) also with a
+// workspace: a call that the allocation-free entry takes always, so that both
+// split alike, any other while it then still splits.
+SplitPlan plan_wide_decode(const kap_kv_cache *kv, int batch, int max_pages, int num_splits) {
   const size_t counters = (size_t)batch * kv->num_kv_heads * sizeof(int32_t) * kap::kTicketStride;
-  return counters > kScratchTicketBytes ? 0 : kScratchBytes - kScratchTicketBytes - 512;
+  const size_t limit =
+      counters > kScratchTicketBytes ? 0 : kScratchBytes - kScratchTicketBytes - 512;
+  const bool noalloc = noalloc_wide_bytes(kv, batch, max_pages, num_splits) <= kScratchBytes;
+  return plan_wide(kv, batch, 1, max_pages, num_splits, limit,
+                   noalloc ? limit : kWidePartialLimit);
 }
 
 // Decode. Tuned path: with num_splits > 0, that many splits for every
@@ -202,7 +250,7 @@ size_t wide_decode_partial_limit(const kap_kv_cache *kv, int batch) {
 // Every other geometry: see plan_wide.
 SplitPlan plan_decode(const kap_kv_cache *kv, int batch, int max_blocks, int num_splits) {
   if (!fast_geometry(kv))
-    return plan_wide(kv, batch, 1, max_blocks, num_splits, wide_decode_partial_limit(kv, batch));
+    return plan_wide_decode(kv, batch, max_blocks, num_splits);
   SplitPlan p{true, false, 1, 0, 0, 0, 0};
   p.slot_rows = 4;
   const int mb = max_blocks > 0 ? max_blocks : 1;
@@ -230,7 +278,8 @@ SplitPlan plan_decode(const kap_kv_cache *kv, int batch, int max_blocks, int num
 // Verify (tuned path): as decode, with page pairs as the work items.
 SplitPlan plan_verify(const kap_kv_cache *kv, int batch, int q_len, int max_pages, int num_splits) {
   if (!fast_geometry(kv) || q_len * 4 > 64)
-    return plan_wide(kv, batch, q_len, max_pages, num_splits, kVerifyPartialLimit);
+    return plan_wide(kv, batch, q_len, max_pages, num_splits, kWidePartialLimit,
+                     kWidePartialLimit);
   SplitPlan p{true, false, 1, 0, 0, 0, 0};
   p.slot_rows = 4 * q_len;
   const int mp = max_pages > 0 ? max_pages : 1;
@@ -316,24 +365,6 @@ void *scratch_base(hipError_t *err) {
     cache[dev] = ptr;
   }
   return cache[dev];
-}
-
-// The allocation-free call takes geometries outside the tuned path as long as
-// uniform splits of at most 64 pages -- finer ones, down to 4 pages, until
-// 4096 (row, split) pairs run, and at least num_splits -- would leave partials
-// that fit the scratch: the bytes of that layout. (What runs needs no more: its
-// split count gives way to the scratch size.)
-size_t noalloc_wide_bytes(const kap_kv_cache *kv, int batch, int max_pages, int num_splits) {
-  const int mb = max_pages > 0 ? max_pages : 1;
-  const long long rows = (long long)batch * kv->num_q_heads;
-  const int lo = cdiv(mb, 64), hi = std::max(lo, cdiv(mb, 4));
-  const long long want = std::max<long long>((4096 + rows - 1) / rows, num_splits);
-  int n = (int)std::min<long long>(std::max<long long>(want, lo), hi);
-  if (num_splits > n) n = std::min(num_splits, mb);
-  n = cdiv(mb, cdiv(mb, n));
-  if (n <= 1) return 0;
-  return kScratchTicketBytes + round_up((size_t)rows * n * kv->head_dim * sizeof(float), 256) +
-         round_up((size_t)rows * n * sizeof(float), 256);
 }
 
 // The static scratch layout for a call whose workspace layout is w (its

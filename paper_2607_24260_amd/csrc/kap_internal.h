@@ -82,7 +82,9 @@ struct AttnArgs {
   int ragged;
   int w_target;                  // balanced mode: workgroups the work is spread over
   int w_uneven;                  // balanced mode, uneven batch: the same, finer
-  int min_chunk;                 // balanced mode: fewest work items per split
+  int min_chunk;                 // balanced mode: fewest work items per split; else (wide
+                                 // kernel): work items per split of a sequence that has fewer
+                                 // than n_split times so many, 0: n_split in any case
   int guess_splits;              // balanced mode: max(1, w_target / (batch * Hkv))
   double rcp_w_target;           // balanced mode: 1 / w_target and 1 / w_uneven (host-rounded)
   double rcp_w_uneven;

@@ -267,3 +267,40 @@ def test_values_near_the_largest_float(kv_dtype, D, G, W, num_splits):
     eo, el = O.selected_decode(pool, q[:, 0].float().cpu().numpy(), lens, fbt, table, [44], 1.0)
     assert_close("decode O", od.cpu().numpy() / big, eo / big, 1e-4)
     assert_close("decode LSE", ld.cpu().numpy(), el, 1e-4)
+
+
+@pytest.mark.parametrize("batch", [64, 70])
+@pytest.mark.parametrize("op", ["decode", "verify"])
+def test_a_long_sequence_among_many_short_ones_is_split(batch, op):
+    # 16 KV heads: with 64 and more sequences every (sequence, KV head) gets a
+    # workgroup four times over; up to 64 sequences the balanced map splits,
+    # above that every sequence by its own length (1030 pages: four pieces of
+    # 258, 300 pages: two). Tolerance: 16480 keys of near-equal weight, whose
+    # float32 sums' errors grow with the square root: 130 * 6e-8, fourfold.
+    D, Hkv, W = 128, 16, 2
+    lens = [1030 * 16, 300 * 16 - 5] + [1 + (7 * i) % 40 for i in range(batch - 2)]
+    r, k, v, sc, fbt = _inputs("bf16", D, Hkv, lens, 31)
+    kv = K.KVCache(k, v, Hkv, torch.bfloat16, sc)
+    q = _query(r, (batch, W, Hkv, D), "bf16")
+    pool = _pool("bf16", k, v, sc)
+    seq, M = dev_i32(lens), fbt.shape[1]
+    heads = (0, 7, 15)
+    for ns in (0, 3):
+        print(f"{op} batch={batch} splits={ns}", flush=True)
+        if op == "verify":
+            assert K.verify_workspace_bytes(kv, batch, W, max(lens), ns) > 0
+            o, lse = K.verify(kv, q, seq, dev_i32(fbt), max(lens), 1.0, num_splits=ns)
+            eo, el = O.verify(pool, q.float().cpu().numpy(), np.asarray(lens), fbt, 1.0,
+                              kv_heads=heads)
+        else:
+            assert K.selected_decode_workspace_bytes(kv, batch, M, ns) > 0
+            nb = [-(-L // 16) for L in lens]
+            vlb = np.tile(np.arange(M, dtype=np.int32), (batch, 1))
+            args = (kv, q[:, 0].contiguous(), seq, dev_i32(fbt), dev_i32(vlb), dev_i32(nb), M, 1.0)
+            o, lse = K.selected_decode(*args, num_splits=ns)
+            eo, el = (x[:, 0] for x in O.verify(pool, q[:, :1].float().cpu().numpy(),
+                                                np.asarray(lens), fbt, 1.0, kv_heads=heads))
+        torch.cuda.synchronize()
+        at = (..., list(heads), slice(None))
+        assert_close("O", o.cpu().numpy()[at], eo[at], TOL)
+        assert_close("LSE", lse.cpu().numpy()[at[:-1]], el[at[:-1]], TOL)
