@@ -234,9 +234,10 @@ kap_status kap_compile_plan_masked(int32_t batch, const int32_t *seq_lens,
  * splits of each (sequence, KV head) on the device from that sequence's
  * actual view, so ragged batches stay balanced; n > 0 forces n key splits
  * per (sequence, KV head) on the tuned path (clamped to max_view_blocks).
- * The wide path (other geometries and dtypes) does the same (over 64
- * sequences, with work for the whole device, it cuts each sequence by its own
- * length). Decode calls that kap_selected_decode_noalloc accepts split no
+ * The wide path (other geometries and dtypes) takes at least n pieces, of at
+ * most 64 pages, when n > 0; with 0 it balances as the tuned path does (over
+ * 64 sequences, with work for the whole device, it cuts each sequence by its
+ * own length). Decode calls that kap_selected_decode_noalloc accepts split no
  * further than its scratch allows, with or without a workspace. Results do
  * not depend on the split count beyond rounding.
  * Passing the full block table as the view, with view_logical_block[b][j] = j

@@ -155,6 +155,7 @@ int blocks_per_cu(int id, int kv_type, int q_len) {
 //    one of `max_pages` fill the device (256 sequences x 8 heads, 64-dim bf16,
 //    one of 128K and 255 of 256 tokens: 166 us, map 78, one split 686; 300 x 1K
 //    tokens, 4-token windows: 234, map 272, one split 233).
+//  * num_splits > 0 asks for at least that many, of at most 64 pages each.
 //  * `partial_limit` bounds the bytes of the split partials of a call that needs
 //    few of them, `partial_most` those of any: split counts give way to them.
 constexpr int kWideUnevenPerCU = 4;
@@ -185,7 +186,7 @@ SplitPlan plan_wide(const kap_kv_cache *kv, int batch, int q_len, int max_pages,
   p.slots = units;
   const long long most = std::max<long long>(1, std::min<long long>(steps, fit_most / units));
   if (num_splits > 0) {
-    p.n_split = (int)std::min<long long>(num_splits, most);
+    p.n_split = (int)std::min<long long>(std::max(num_splits, cdiv(max_pages, 64)), most);
     p.slots = units * p.n_split;
   } else if (full && max_pages <= 64) {
     // short sequences: one split each

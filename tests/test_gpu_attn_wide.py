@@ -285,7 +285,7 @@ def test_a_long_sequence_among_many_short_ones_is_split(batch, op):
     pool = _pool("bf16", k, v, sc)
     seq, M = dev_i32(lens), fbt.shape[1]
     heads = (0, 7, 15)
-    for ns in (0, 3):
+    for ns in (0, 1):                       # 1: pieces of at most 64 pages (17 for the longest)
         print(f"{op} batch={batch} splits={ns}", flush=True)
         if op == "verify":
             assert K.verify_workspace_bytes(kv, batch, W, max(lens), ns) > 0
@@ -304,3 +304,15 @@ def test_a_long_sequence_among_many_short_ones_is_split(batch, op):
         at = (..., list(heads), slice(None))
         assert_close("O", o.cpu().numpy()[at], eo[at], TOL)
         assert_close("LSE", lse.cpu().numpy()[at[:-1]], el[at[:-1]], TOL)
+
+
+def test_a_split_count_is_a_least_count_outside_the_tuned_geometry():
+    # pieces of at most 64 pages, whatever count is asked for
+    k = torch.zeros((4, 2, 8, 16, 8), device="cuda")
+    v = torch.zeros((4, 2, 64, 16), device="cuda")
+    kv = K.KVCache(k, v, 4, torch.float32)
+    size = lambda ns, pages=256: K.selected_decode_workspace_bytes(kv, 1, pages, ns)
+    assert size(1) == size(2) == size(4) > 0 and size(8) > size(4)
+    assert size(1, 64) == 0
+    size = lambda ns: K.verify_workspace_bytes(kv, 1, 3, 256 * 16, ns)
+    assert size(1) == size(4) > 0
