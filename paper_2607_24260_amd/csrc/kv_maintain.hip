@@ -67,11 +67,17 @@ __global__ __launch_bounds__(kThreads) void append_kv_kernel(AppendArgs a) {
 //    page it turns the 16 x 4 bytes around in registers, giving the 64
 //    contiguous bytes of its rows, which go out through LDS so that a store
 //    instruction covers 1 KB; other tokens are stored as single elements.
-// All loads of a workgroup are in flight together: at one token per sequence
+// Tokens outside whole pages are also shared out over blockIdx.z: with few of
+// them the workgroups are few, and one that moves 16 tokens one after the other
+// takes as long (8 KV heads of 128 dims, fp8: 64 tokens in 64 places 3.9 us, one
+// workgroup for all 16 tokens 9.9; 64 windows of 5 tokens 4.4, 10.2). Up to
+// kAppendWorkgroups in all: more find nothing to do.
+// All loads of a whole page are in flight together: at one token per sequence
 // latency is all there is, at whole pages HBM: 4 x 2048 bf16 tokens, 8 KV heads
 // of 128 dims (67 MB) in 24.9 us per call; one workgroup per token with
 // 2-byte stores 16 and 32 bytes apart took 49 us. (Nontemporal loads: 30 us -- new
 // tokens come from the caches of the kernels that made them.)
+constexpr int kAppendWorkgroups = 1024;
 template <int ES>
 __device__ __forceinline__ void transpose_column(const uint32_t x[kPage], uint32_t o[kPage]) {
   // o: rows of the column's dims, 4 ES dwords each
@@ -130,8 +136,11 @@ __global__ __launch_bounds__(kThreads) void append_runs_kernel(AppendArgs a) {
                      ((joined >> first >> 1) & 0x7FFFu) == 0x7FFFu;
   const bool mine = lane >= kPage && lane < 2 * kPage;
   const unsigned long long starts = __ballot(mine && whole && off == 0);   // at most one
-  const unsigned single = (unsigned)(__ballot(mine && good && !whole) >> kPage);
-  if (blockIdx.y == 0 && threadIdx.x < 64 && mine && slot >= 0 && !good && a.bad_slots)
+  // of the other tokens, this workgroup's share
+  const unsigned single = (unsigned)(__ballot(mine && good && !whole &&
+                                              lane % gridDim.z == blockIdx.z) >> kPage);
+  if (blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 64 && mine && slot >= 0 && !good &&
+      a.bad_slots)
     atomicAdd(a.bad_slots, 1);
 
   auto slot_at = [&](int l) {                  // slot of lane l (the same l in every lane)
@@ -168,7 +177,7 @@ __global__ __launch_bounds__(kThreads) void append_runs_kernel(AppendArgs a) {
         x[i] = src[(size_t)i * cols];
   };
 
-  if (starts) {
+  if (starts && blockIdx.z == 0) {
     const int f = __builtin_ctzll(starts);     // lane
     const int64_t to = slot_at(f);
     const int token = t0 - kPage + f;
@@ -207,17 +216,34 @@ __global__ __launch_bounds__(kThreads) void append_runs_kernel(AppendArgs a) {
       const bool live = (single >> i) & 1u;
       move_k(live ? t0 + i : t0, live, live ? to : 0);
     } else {
-      uint32_t x[kPage];
-      load_v(t0, single, x);
+      // element by element, so that a store instruction covers 64 neighbouring
+      // rows; more tokens at a time cost the small calls code to fetch
+      const elem *src = static_cast<const elem *>(a.v_new) + (size_t)t0 * row;
+      const size_t e0 = (size_t)part * kThreads * kColDims + threadIdx.x;
+      for (unsigned left = single; left;) {
+        constexpr int kBatch = ES == 4 ? 8 : 4;
+        int token[kBatch];
+        elem x[kBatch][kColDims];
 #pragma unroll
-      for (int i = 0; i < kPage; ++i)
-        if (col < cols && ((single >> i) & 1u)) {
-          const int64_t to = slot_at(kPage + i);
-          elem *dst = static_cast<elem *>(a.v_pages) + (size_t)(to / kPage) * row * kPage +
-                      (size_t)col * kColDims * kPage + (to & (kPage - 1));
+        for (int i = 0; i < kBatch; ++i) {
+          token[i] = left ? __builtin_ctz(left) : -1;
+          left &= left - 1;
 #pragma unroll
-          for (int e = 0; e < kColDims; ++e) dst[e * kPage] = (elem)(x[i] >> (8 * ES * e));
+          for (int e = 0; e < kColDims; ++e)
+            if (token[i] >= 0 && e0 + e * kThreads < row)
+              x[i][e] = src[token[i] * row + e0 + e * kThreads];
         }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+          if (token[i] < 0) continue;
+          const int64_t to = slot_at(kPage + token[i]);
+          elem *dst = static_cast<elem *>(a.v_pages) + (size_t)(to / kPage) * row * kPage +
+                      (to & (kPage - 1));
+#pragma unroll
+          for (int e = 0; e < kColDims; ++e)
+            if (e0 + e * kThreads < row) dst[(e0 + e * kThreads) * kPage] = x[i][e];
+        }
+      }
     }
   }
 }
@@ -278,7 +304,8 @@ hipError_t launch_append_kv(const AppendArgs &a, hipStream_t s) {
     return hipGetLastError();
   }
   const long long cols = (long long)a.Hkv * a.D * a.elem_bytes / 4;
-  const dim3 grid((a.num_tokens + kPage - 1) / kPage, 2 * (unsigned)((cols + kThreads - 1) / kThreads));
+  dim3 grid((a.num_tokens + kPage - 1) / kPage, 2 * (unsigned)((cols + kThreads - 1) / kThreads));
+  while (grid.z < kPage && 2ll * grid.x * grid.y * grid.z <= kAppendWorkgroups) grid.z *= 2;
   switch (a.elem_bytes) {
     case 4: hipLaunchKernelGGL(append_runs_kernel<4>, grid, dim3(kThreads), 0, s, a); break;
     case 2: hipLaunchKernelGGL(append_runs_kernel<2>, grid, dim3(kThreads), 0, s, a); break;

@@ -206,3 +206,25 @@ def test_append_runs_bit_exact(dtype, Hkv, D, aligned):
     assert int(bad.item()) == want_bad > 0
     assert np.array_equal(got.k_pages, want.k_pages)
     assert np.array_equal(got.v_pages, want.v_pages)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("n", [1, 5, 16, 17, 300, 1500, 3000])
+def test_append_scattered_tokens_bit_exact(dtype, n):
+    # tokens in slots of their own, some not to be stored, beside two whole
+    # pages: shared out over 16 workgroups (few tokens) down to one
+    Hkv, D = 8, 128
+    kv = small_pool(dtype, num_pages=n // 8 + 6, Hkv=Hkv, D=D)
+    before = host_pool(kv, dtype)
+    r = np.random.default_rng(n)
+    slots = 32 + r.permutation(16 * (n // 8 + 4))[:n].astype(np.int64)
+    slots[r.random(n) < 0.1] = -1
+    if n >= 300:
+        slots[100:132] = np.arange(32)
+    k_new, v_new = (new_tokens(n, Hkv, D, dtype, s) for s in (4, 5))
+    K.append_kv(kv, k_new, v_new, torch.as_tensor(slots).cuda())
+    torch.cuda.synchronize()
+    want, _ = O.append_kv(before, to_host_bits(k_new, dtype), to_host_bits(v_new, dtype), slots)
+    got = host_pool(kv, dtype)
+    assert np.array_equal(got.k_pages, want.k_pages)
+    assert np.array_equal(got.v_pages, want.v_pages)
