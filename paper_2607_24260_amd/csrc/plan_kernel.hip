@@ -24,9 +24,12 @@ namespace kap {
 namespace {
 
 constexpr int kRankChunk = 2048;   // ranking keys staged per pass; also the LDS view list
-// Spans ranked by counting all pairs; more are ranked by buckets (187 spans:
-// 12.8 us per call by pairs, 9.0 by buckets; at 118 both took 10.5).
-constexpr int kPairsMost = 128;
+// Spans ranked by counting all pairs; more are ranked by buckets. Up to half
+// the threads two or more of them share a span's pairs (4 x 128K, 5.5%, per call:
+// 96 spans 11.1 us by pairs, 11.6 by buckets; 112: 11.5, 11.7; 128: 11.6, 11.9),
+// above it one counts them all (136: 14.2, 12.5; 160: 15.0, 12.8). Token-granular
+// and 64 x 16K plans cross at the same place.
+constexpr int kPairsMost = kPlanThreads / 2;
 // Most spans in one bucket: a span counts its bucket's spans before it, so
 // one of 512 costs about as much as all pairs among 700 spans.
 constexpr int kBucketMost = 512;
