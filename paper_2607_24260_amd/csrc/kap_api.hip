@@ -635,7 +635,6 @@ static kap_status selected_decode(const kap_kv_cache *kv, int32_t batch, const v
   a.kv_scales = kv->kv_scales;
   a.num_pages = kv->num_pages;
   a.q = q;
-  a.q_f32 = kv->q_dtype == KAP_DT_F32;
   a.q_len = 1;
   a.seq_lens = seq_lens;
   // An empty view may come with NULL tables: point them at seq_lens (row
@@ -825,7 +824,6 @@ kap_status kap_verify(const kap_kv_cache *kv, int32_t batch, int32_t q_len, cons
   a.kv_scales = kv->kv_scales;
   a.num_pages = kv->num_pages;
   a.q = q;
-  a.q_f32 = kv->q_dtype == KAP_DT_F32;
   a.q_len = q_len;
   a.seq_lens = seq_lens;
   a.block_table = full_block_table;

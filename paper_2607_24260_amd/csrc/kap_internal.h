@@ -60,8 +60,7 @@ struct AttnArgs {
   const void *v_pages;
   const float *kv_scales;
   int64_t num_pages;
-  const void *q;          // [batch][q_len][Hq][D], bf16 or f32
-  int q_f32;              // 1 if q is float32
+  const void *q;          // [batch][q_len][Hq][D], float32 with float32 KV, else bf16
   int q_len;
   const int32_t *seq_lens;
   const int32_t *block_table;    // decode: view table; verify: full table
@@ -77,8 +76,9 @@ struct AttnArgs {
   int row_blocks;
   int row_tiles;
   // Balanced mode (ragged != 0): split counts per sequence come from its
-  // actual work on the device (see ragged_map); blockIdx.x is the partial
-  // slot. Otherwise the grid is (n_split, Hkv, batch).
+  // actual work on the device (see ragged_map); the workgroup's index is the
+  // partial slot. Otherwise the grid holds n_split splits of every (sequence,
+  // KV head).
   int ragged;
   int w_target;                  // balanced mode: workgroups the work is spread over
   int w_uneven;                  // balanced mode, uneven batch: the same, finer
@@ -94,8 +94,9 @@ struct AttnArgs {
   // slot0 + n - 1.
   float *part_o;    // normalised partial outputs
   float *part_lse;  // log2-domain partial LSE
-  int32_t *tickets; // [batch][Hkv][kTicketStride] arrival counters of the fused merge
-                    // (element 0 of each block; zero between calls)
+  int32_t *tickets; // [batch][Hkv][kTicketStride] arrival counters of the fused merge, zero
+                    // between calls (tuned kernels: element 0 of each block; wide kernel: row
+                    // block rb counts in element rb % kTicketStride)
   // decode over a token-granular view: [batch][bt_stride] masks, bit t = token
   // t of the view page is visible; NULL: every token below seq_len is
   const uint32_t *token_mask = nullptr;
@@ -203,13 +204,6 @@ int verify_mfma_blocks_per_cu(int kv_type, int q_len);
 // device helpers
 // ---------------------------------------------------------------------------
 
-// Streaming load of KV data: every KV byte is read once per call, so the
-// loads are nontemporal (they measurably raise achieved HBM read bandwidth).
-template <typename T>
-__device__ __forceinline__ T load_stream(const T *p) {
-  return __builtin_nontemporal_load(p);
-}
-
 // Buffer descriptor of one (page, KV head) tile of `bytes` bytes at
 // base + byte_off (wave-uniform). Loads through it take a per-lane byte
 // offset, are bounds-checked by the hardware (reads past `bytes` return 0) and
@@ -232,10 +226,6 @@ template <int POLICY = kNonTemporal>
 __device__ __forceinline__ kv_u32x2 tile_load8(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_bit_cast(kv_u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, POLICY));
 }
-__device__ __forceinline__ uint32_t tile_load4(__amdgpu_buffer_rsrc_t r, int off) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kNonTemporal);
-}
-
 // Block-table entries read ahead through the vector memory pipe. A scalar
 // load of the next entry, waited for right before the page load that needs
 // it, stalls the wavefront for a full cache round trip on every page; a
@@ -276,20 +266,6 @@ __device__ __forceinline__ float2 page_scales(const float *kv_scales, int page, 
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-
-// Round-to-nearest-even float -> bfloat16 bits (finite inputs).
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
-// Two OCP E4M3FN codes (bytes 0,1 or 2,3 of w) -> two floats, exact.
-template <bool HIGH>
-__device__ __forceinline__ float2 fp8x2_to_f32(uint32_t w) {
-  auto v = __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w), HIGH);
-  return make_float2(v[0], v[1]);
-}
 
 // Four E4M3FN codes (one dword) -> two dwords of bf16 pairs, exact (every
 // E4M3FN value, subnormals included, is a bf16 value); unit scale.
@@ -359,22 +335,6 @@ __device__ __forceinline__ float max_abs(float m, kv_f32x4 x) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) m = max_f(m, __builtin_fabsf(x[e]));
   return m;
-}
-
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-__device__ __forceinline__ int wave_sum_i(int x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
 }
 
 // ---------------------------------------------------------------------------
@@ -590,28 +550,10 @@ __device__ __forceinline__ bool last_arrival(const AttnArgs &a, int b, int g, in
   return *flag != 0;
 }
 
-// last_arrival for a workgroup whose wavefronts may all have written part of
-// its partial: each waits until its own stores are complete, the workgroup
-// meets at a barrier, and one thread takes the ticket.
-__device__ __forceinline__ bool last_arrival_all(const AttnArgs &a, int b, int g, int n_split,
-                                                 int *flag) {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's stores are complete
-  asm volatile("" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t *ctr = a.tickets + ((size_t)b * a.Hkv + g) * kTicketStride;
-    const int prev = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int last = (prev == n_split - 1) ? 1 : 0;
-    if (last) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *flag = last;
-  }
-  __syncthreads();
-  return *flag != 0;
-}
-
-// The same for any counter: true in every thread of the workgroup that takes
-// the last of `expected` tickets.
+// The same for a workgroup whose wavefronts may all have written part of its
+// partial, and any counter: true in every thread of the workgroup that takes
+// the last of `expected` tickets. Each wavefront waits until its own stores are
+// complete, the workgroup meets at a barrier, and one thread takes the ticket.
 __device__ __forceinline__ bool last_arrival_of(int32_t *ctr, int expected, int *flag) {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's stores are complete
@@ -625,6 +567,10 @@ __device__ __forceinline__ bool last_arrival_of(int32_t *ctr, int expected, int 
   }
   __syncthreads();
   return *flag != 0;
+}
+__device__ __forceinline__ bool last_arrival_all(const AttnArgs &a, int b, int g, int n_split,
+                                                 int *flag) {
+  return last_arrival_of(a.tickets + ((size_t)b * a.Hkv + g) * kTicketStride, n_split, flag);
 }
 
 // LSE merge of the ns partials (slots slot0 .. slot0 + ns - 1) of the R_loc

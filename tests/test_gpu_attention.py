@@ -440,7 +440,7 @@ def test_peaky_planted_keys(alpha, kv_dtype):
 
 
 # --------------------------------------------------------------------------
-# every geometry the ABI accepts: the generic path (any GQA ratio, head_dim
+# every geometry the ABI accepts: the wide path (any GQA ratio, head_dim
 # 64 / 128 / 256) for bf16 and fp8 pools, one and several key splits
 # --------------------------------------------------------------------------
 
@@ -464,10 +464,9 @@ def _window(w, q_len, seed):
 @pytest.mark.parametrize("D,Hq,Hkv", [(64, 8, 4), (256, 16, 2), (128, 16, 8), (128, 32, 4)])
 @pytest.mark.parametrize("L,num_splits", [(900, 0), (3000, 0), (3000, 7)])
 def test_generic_path_geometries(kv_dtype, D, Hq, Hkv, L, num_splits):
-    # lengths L, L - 1 and 37 (partial last pages); with this few query rows
-    # the generic path splits the keys into pieces of 4 pages and more (9-15
-    # splits at 900 tokens, 9-47 at 3000, by call); num_splits = 7 asks for
-    # at least seven
+    # lengths L, L - 1 and 37 (partial last pages): the balanced map cuts them
+    # into splits of at least four steps of two pages (up to 8 at 900 tokens, 24
+    # at 3000); num_splits = 7 asks for at least seven
     cfg = 2 if kv_dtype == "bf16" else 5
     # (the ragged fp8 recipe draws its lengths from [4096, seq_len])
     w, pool = _ragged(cfg, 3, max(L, 1000) if cfg == 2 else 5000, [L, L - 1, 37],
@@ -491,7 +490,7 @@ def test_out_of_pool_page_ids_contribute_no_keys(kv_dtype, D):
     # the library is told the pool holds fewer pages than the tensors do, so
     # the ids past that count name allocated memory that must still not be
     # read; views and tables also carry negative ids. D = 128 runs the tuned
-    # kernels, D = 64 / 256 the generic path.
+    # kernels, D = 64 / 256 the wide one.
     cfg = 2 if kv_dtype == "bf16" else 5
     w, _ = workload(cfg, batch=3, seq_len=5000, n_decode=1, n_verify=1, head_dim=D)
     small = w.num_pages - w.num_pages // 4
@@ -533,7 +532,7 @@ def test_out_of_pool_page_ids_contribute_no_keys(kv_dtype, D):
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
 def test_shared_workspace(kv_dtype):
     # one workspace serves decode and verify calls of the tuned kernels
-    # (balanced and uniform splits) and of the generic path in turn, so each
+    # (balanced and uniform splits) and of the wide one in turn, so each
     # call finds the previous calls' partials in it; after every call
     # its arrival-counter block is zero again, and every result equals the
     # same call's result with a fresh workspace

@@ -6,7 +6,7 @@ unchanged view skip the map. The scheduled call must return exactly the
 unscheduled call's results (same split assignment, same kernels): checked bit
 for bit on the bf16 workloads, the ragged fp8 workload and a token-granular
 view, reused over several proposal steps, under HIP-graph replay, and against
-the oracle on one workload. Calls without a balanced map (the generic path,
+the oracle on one workload. Calls without a schedule (the wide path,
 or one split per (sequence, KV head)) take an empty schedule.
 """
 import numpy as np
@@ -179,7 +179,7 @@ def test_graph_replays_of_scheduled_decode():
 
 
 def test_empty_schedule_without_balanced_map():
-    # fp32 goes through the generic path: no map, no schedule
+    # fp32 goes through the wide path: no schedule
     w = make_workload(1, device="cuda")
     kv = kv_of(w)
     plan, cap, _ = _view(w)

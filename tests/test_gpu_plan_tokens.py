@@ -188,7 +188,7 @@ def token_plan(w, capacity=None):
 
 
 @pytest.mark.parametrize("config,kw,num_splits", [
-    (1, {}, 0),                                         # fp32: generic path
+    (1, {}, 0),                                         # fp32: wide path
     (1, {}, 3),
     (2, dict(batch=3, seq_len=6000), 0),                # bf16: tuned, balanced map
     (2, dict(batch=3, seq_len=6000), 2),                # bf16: tuned, uniform splits

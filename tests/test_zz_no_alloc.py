@@ -2,7 +2,7 @@
 callers that cannot allocate) against kap_selected_decode with a workspace:
 two calls in a row through the C ABI, the second with a smaller input, each
 matching the workspace call to the parity bar (and in fact bit for bit: the
-same kernels run on the same inputs), plus a generic-path call and the size
+same kernels run on the same inputs), plus a wide-path call and the size
 limits."""
 import numpy as np
 import pytest
@@ -46,21 +46,22 @@ def test_two_calls_in_a_row_second_smaller():
 
 
 def test_generic_path_and_repeat():
-    # head_dim 64 (generic kernel + separate merge, partials in the scratch),
+    # head_dim 64 (wide kernel, partials and counters in the scratch),
     # twice, then the tuned path again: the scratch keeps nothing a call needs
-    print("noalloc: generic path D=64, bf16", flush=True)
+    print("noalloc: wide path D=64, bf16", flush=True)
     w = make_workload(2, device="cuda", batch=3, seq_len=3000, n_decode=2, n_verify=1,
                       head_dim=64)
     _both(w, step=0)
     _both(w, step=1)
-    print("noalloc: tuned path after the generic one", flush=True)
+    print("noalloc: tuned path after the wide one", flush=True)
     w = make_workload(2, device="cuda", batch=2, seq_len=2000, n_decode=1, n_verify=1)
     _both(w)
 
 
 def test_calls_beyond_the_scratch_are_refused_before_launch():
-    # generic path (fp32): 8 sequences x 32 heads x 128 splits of partials
-    # (> 16 MiB) -- refused; the pool and tables are tiny, nothing runs
+    # wide path (fp32): 8 sequences x 32 heads x 128 uniform splits of 64 pages
+    # would leave partials of more than 16 MiB -- refused; the pool and tables
+    # are tiny, nothing runs
     print("noalloc: size limits", flush=True)
     dev = "cuda"
     B, Hq, Hkv, D, cap = 8, 32, 8, 128, 8192
