@@ -102,26 +102,31 @@ def test_rows_and_splits(kv_dtype, D, G, W):
             assert_close("decode LSE", lse.cpu().numpy(), el, TOL)
 
 
-@pytest.mark.parametrize("kv_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kv_dtype", ["f32", "bf16", "fp8"])
 @pytest.mark.parametrize("num_splits", [0, 1, 3])
 def test_infinities_and_nans_in_v_reach_only_the_rows_that_see_them(kv_dtype, num_splits):
     # a window of 4 over 70 tokens: V of token 67 is +inf in dim 3, of token 68
     # -inf in dim 5, of token 69 NaN in dim 7 (rows 1.., 2.. and 3 see them);
-    # the slots past the end hold NaN, K included
+    # the slots past the end hold NaN, K included (fp8 has no infinities: NaN)
     D, G, W, L = 64, 3, 4, 70
+    fp8 = kv_dtype == "fp8"
+    nan = 0x7F if fp8 else np.nan
     r, k, v, sc, fbt = _inputs(kv_dtype, D, 1, [L], 5)
+    clean_k, clean = k.clone(), v.clone()
     for tok, dim, x in ((67, 3, np.inf), (68, 5, -np.inf), (69, 7, np.nan)):
-        v[int(fbt[0, tok // 16]), 0, dim, tok % 16] = x
+        v[int(fbt[0, tok // 16]), 0, dim, tok % 16] = nan if fp8 else x
+        clean[int(fbt[0, tok // 16]), 0, dim, tok % 16] = 0
     last = int(fbt[0, L // 16])
-    v[last, 0, :, L % 16:] = np.nan
-    k[last, 0, :, L % 16:] = np.nan
+    k[last, 0, :, L % 16:] = nan
+    v[last, 0, :, L % 16:] = nan
+    clean_k[last, 0, :, L % 16:] = 0
+    clean[last, 0, :, L % 16:] = 0
     kv = K.KVCache(k, v, G, _query(r, (1, 1), kv_dtype).dtype, sc)
     q = _query(r, (1, W, G, D), kv_dtype)
-    clean = v.clone()
-    clean[~torch.isfinite(clean)] = 0
-    eo, el = O.verify(_pool(kv_dtype, torch.nan_to_num(k.float()).to(k.dtype), clean, sc),
+    eo, el = O.verify(_pool(kv_dtype, clean_k, clean, sc),
                       q.float().cpu().numpy(), np.asarray([L]), fbt, 1.0)
-    eo[:, 1:, :, 3], eo[:, 2:, :, 5], eo[:, 3:, :, 7] = np.inf, -np.inf, np.nan
+    inf = np.nan if fp8 else np.inf
+    eo[:, 1:, :, 3], eo[:, 2:, :, 5], eo[:, 3:, :, 7] = inf, -inf, np.nan
     o, lse = K.verify(kv, q, dev_i32([L]), dev_i32(fbt), L, 1.0, num_splits=num_splits)
     torch.cuda.synchronize()
     o = o.cpu().numpy()
@@ -133,11 +138,13 @@ def test_infinities_and_nans_in_v_reach_only_the_rows_that_see_them(kv_dtype, nu
 
 @pytest.mark.parametrize("kv_dtype,D,G", [("bf16", 128, 4), ("fp8", 128, 4), ("bf16", 64, 3),
                                           ("fp8", 256, 4), ("f32", 128, 4)])
-@pytest.mark.parametrize("step", [3.5, -3.5, 7.0])
+@pytest.mark.parametrize("step", [0.3, 0.7, -0.7, 3.5, -3.5, 7.0])
 def test_logits_that_climb_from_page_to_page(kv_dtype, D, G, step):
-    # every key of page p has the logit step * (p - 30): about 5 or 10 powers of
-    # two between pages, so that the softmax reference stays behind by less
-    # than its allowance or has to move, upwards from -105 or downwards; fp8
+    # every key of page p has the logit step * (p - 30). A wavefront's pages are
+    # four apart (eight with two-page steps, more with splits): with 0.3 and 0.7
+    # it climbs by 1.7 to 8 powers of two a step, so that several steps weigh up
+    # to 2^8 against an older reference before it moves; with 3.5 and 7 (20 and
+    # more) it moves at every step, upwards from -105; downwards it stays. fp8
     # page scales carry the value, negative ones included. Weights of the
     # tuned kernels are rounded to 2^-16 (of values up to about 4: 6e-5), LSEs
     # of up to 210 to a few 2^-23 of that.
