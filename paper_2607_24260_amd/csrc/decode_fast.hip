@@ -430,7 +430,7 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
   PageRegs<KV> r[RING];
   int pg[RING];
   uint32_t nv[RING];
-  for (;;) {
+  auto walk = [&] {
     // (each slot's table reads follow its page loads, as in the loop, so the
     // wait counts at the loop header are the steady-state ones)
 #pragma unroll
@@ -454,14 +454,18 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
 #pragma unroll
     for (int j = 0; j < RING - 1; ++j)
       if (full + j < n_my) process(r[j], pg[j], nv[j]);
-    const float t = max_abs(max_abs(0.f, o_lo), o_hi);
-    if (defer == 0.f || !__any(!(t < kLargeSum))) break;
+  };
+  walk();
+  if (__any(!(max_abs(max_abs(0.f, o_lo), o_hi) < kLargeSum))) {
+    // (a copy of the walk: in a loop over both, what the second shares with the
+    // first is computed before the first page loads: 16K batch 18.0 vs 17.7 us)
     defer = 0.f;
     m_c = kNoMax;
     l_c = 0.f;
     o_lo = f32x4{0.f, 0.f, 0.f, 0.f};
     o_hi = f32x4{0.f, 0.f, 0.f, 0.f};
     first_entries(wi);
+    walk();
   }
 
   // ---- per-wave totals -------------------------------------------------------
