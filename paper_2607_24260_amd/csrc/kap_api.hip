@@ -607,8 +607,10 @@ static kap_status selected_decode(const kap_kv_cache *kv, int32_t batch, const v
                                : noalloc_wide_bytes(kv, batch, max_view_blocks, num_splits);
     if (need > kScratchBytes)
       return fail(KAP_ERR_WORKSPACE_TOO_SMALL,
-                  "the call's split partials need %zu bytes; the allocation-free call's scratch "
-                  "holds %zu (use kap_selected_decode with a workspace)",
+                  "%s %zu bytes; the allocation-free call's scratch holds %zu (use "
+                  "kap_selected_decode with a workspace)",
+                  p.fast ? "the call's split partials need"
+                         : "partials of uniform splits of at most 64 pages would need",
                   need - kScratchTicketBytes, kScratchBytes - kScratchTicketBytes);
     hipError_t e = hipSuccess;
     workspace = scratch_base(&e);
