@@ -26,8 +26,8 @@
 // rate; for a single short sequence, launch, first loads and the merge (about
 // 5 + 4 us). One wavefront per query row with vector dot products, which this
 // replaces, read KV q_len * G times: 8 x 16K, 64-dim heads, 5-token windows
-// 402 -> 47 us; 8 x 32K views of 15%, 8 heads per KV head 190 -> 20.6 us;
-// 4K float32, 5-token window 120 -> 19 us.
+// 402 -> 47 us; 8 x 32K views of 15%, 8 heads per KV head 190 -> 20.0 us;
+// 4K float32, 5-token window 120 -> 17.7 us.
 #include "kap_internal.h"
 
 #include <type_traits>
