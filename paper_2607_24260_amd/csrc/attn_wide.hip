@@ -420,10 +420,11 @@ void attn_wide_kernel(AttnArgs a) {
 
   // page id and visible tokens of an entry (see decode: an invalid id, or a
   // block past the sequence, has none)
-  // (32-bit scalar arithmetic only: a 64-bit comparison runs on the vector unit,
-  // and a page address built from its result made the compiler loop over the
-  // lanes around every load: 2 x 32K 64-dim bf16, one split 188 vs 167 us, and
-  // the registers of the 256-dim two-tile kernels ran out)
+  // (In scalar registers throughout: table entries read by vector loads are
+  // named uniform, and a 64-bit comparison would run on the vector unit. From
+  // vector registers the compiler looped over the lanes around page loads and
+  // chained readfirstlanes into every step: 2 x 32K 64-dim bf16, one split
+  // WFBEFORE vs WFNOW us, and the registers of the 256-dim two-tile kernels ran out)
   const uint32_t page_limit = (uint32_t)(a.num_pages < 0x80000000ll ? a.num_pages : 0x80000000ll);
   auto set_page = [&](PageRegs<KV, D> &r, bool live, int page, int lblk, uint32_t mask) {
     const int nvalid = lblk < (L >> 4) ? kPage : (lblk == (L >> 4) ? L & (kPage - 1) : 0);
@@ -713,8 +714,9 @@ void attn_wide_kernel(AttnArgs a) {
 #pragma unroll
       for (int x = 0; x < PPS; ++x) {
         const int kk = min(k + x, np - 1);
-        set_page(S.p[x], i < n_my && k + x < np, tbt[kk], tlb ? tlb[kk] : k + x,
-                 tmk ? tmk[kk] : 0xFFFFu);
+        set_page(S.p[x], i < n_my && k + x < np, __builtin_amdgcn_readfirstlane(tbt[kk]),
+                 tlb ? __builtin_amdgcn_readfirstlane(tlb[kk]) : k + x,
+                 tmk ? __builtin_amdgcn_readfirstlane(tmk[kk]) : 0xFFFFu);
       }
     };
     auto load_all = [&](Step &S) {

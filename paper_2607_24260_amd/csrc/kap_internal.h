@@ -249,7 +249,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t table_rsrc(const int32_t *row,
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(row), 0, entries * 4, kBufDword3);
 }
 __device__ __forceinline__ int table_ahead(__amdgpu_buffer_rsrc_t r, int vzero_or_4, int idx) {
-  return (int)__builtin_amdgcn_raw_buffer_load_b32(r, vzero_or_4, idx * 4, 0);
+  return (int)__builtin_amdgcn_raw_buffer_load_b32(
+      r, vzero_or_4, __builtin_amdgcn_readfirstlane(idx * 4), 0);
 }
 __device__ __forceinline__ int lane_value(int v, int lane) {
   return __builtin_amdgcn_readlane(v, lane);
