@@ -233,7 +233,8 @@ __device__ __forceinline__ kv_u32x2 tile_load8(__amdgpu_buffer_rsrc_t r, int off
 // round before its use and waited for with the page data. `opaque_zero` is a
 // VGPR the compiler cannot see through (so the load stays a vector load);
 // lane l reads element idx + (l & 1) of the table row, so lanes 0 and 1 hold
-// two consecutive entries. Reads past the row's `bytes` return 0.
+// two consecutive entries. Reads past the row's `bytes` return 0. (idx is the
+// same in every lane, and is said to be, or the compiler may loop over the lanes.)
 __device__ __forceinline__ int opaque_zero() {
   int z;
   asm volatile("v_mov_b32 %0, 0" : "=v"(z));
