@@ -331,16 +331,14 @@ __global__ __launch_bounds__(256) void decode_fast_kernel(AttnArgs a) {
   // is invalid, the block lies past the sequence, or i is past this
   // wavefront's entries): tokens below the sequence length, and with a token
   // mask only those whose bit is set.
+  // (32-bit scalar arithmetic without branches)
+  const uint32_t page_limit = (uint32_t)(a.num_pages < 0x80000000ll ? a.num_pages : 0x80000000ll);
   auto validate = [&](bool live, int raw_page, int raw_lblk, uint32_t raw_mask, int &page,
                       uint32_t &vis) {
-    const long long rem = (long long)L - (long long)raw_lblk * kPage;
-    const int nvalid = (int)(rem < 0 ? 0 : (rem > kPage ? kPage : rem));
-    vis = (0xFFFFu >> (kPage - nvalid)) & raw_mask;
-    page = raw_page;
-    if (page < 0 || (int64_t)page >= a.num_pages || !live) {
-      vis = 0u;
-      page = 0;
-    }
+    const int nvalid = raw_lblk < (L >> 4) ? kPage : (raw_lblk == (L >> 4) ? L & (kPage - 1) : 0);
+    const bool ok = live & ((uint32_t)raw_page < page_limit);
+    vis = ok ? (0xFFFFu >> (kPage - nvalid)) & raw_mask : 0u;
+    page = ok ? raw_page : 0;
   };
   auto page_info = [&](bool live, int j, int &page, uint32_t &vis) {   // entries from table_issue
     validate(live, lane_value(ahead_pg[j], 0), lane_value(ahead_lb[j], 0),

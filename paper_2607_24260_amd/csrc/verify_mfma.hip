@@ -181,8 +181,10 @@ __device__ __forceinline__ void vt_tiles(const u32x4 rows[2], uint32_t out[8]) {
 template <int KV>
 __device__ __forceinline__ void load_pair_k(PairRegs<KV> &r, const AttnArgs &a, int pa, int pb,
                                             int g, int n, int j, bool live) {
-  r.okA = live && pa >= 0 && (int64_t)pa < a.num_pages;
-  r.okB = live && pb >= 0 && (int64_t)pb < a.num_pages;
+  // (32-bit scalar comparisons without branches; a negative id is a large one)
+  const uint32_t limit = (uint32_t)(a.num_pages < 0x80000000ll ? a.num_pages : 0x80000000ll);
+  r.okA = live & ((uint32_t)pa < limit);
+  r.okB = live & ((uint32_t)pb < limit);
   r.pA = r.okA ? pa : 0;
   r.pB = r.okB ? pb : 0;
   const size_t tile = kTileBytes(KV);
