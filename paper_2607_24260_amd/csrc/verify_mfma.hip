@@ -309,7 +309,12 @@ void verify_mfma_kernel(AttnArgs a) {
   int lim[NT];                       // row sees logical positions < lim
   float m[NT], l[NT];
   f32x4 acc[NT][8];
-  float defer = kDefer;              // 0 in a second walk, see kLargeSum
+  // A reference that moves late, with the second walk it may need (see
+  // kLargeSum) -- except in the three-tile bf16 kernels, which lose more to the
+  // loop over the walks than they gain (8 x 12K, 9 tokens: 77.9 vs 74.3 us; 4 x
+  // 32K 94.6 vs 92.6).
+  constexpr bool kLate = KV == kFP8 || NT != 3;
+  float defer = kLate ? kDefer : 0.f;   // 0 in a second walk
   const int last_full = (L - a.q_len) / kPage;   // pages below this are fully visible to all rows
   // C4 tile: rows 16 (NT - 1) .. + 3 are the four heads of window token
   // 4 (NT - 1), which sees logical positions below lim_c4
@@ -607,7 +612,7 @@ void verify_mfma_kernel(AttnArgs a) {
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) t = max_abs(t, acc[nt][dt]);
-    if (defer == 0.f || !__any(!(t < kLargeSum))) break;
+    if (!kLate || defer == 0.f || !__any(!(t < kLargeSum))) break;
     defer = 0.f;
   }
 
