@@ -310,10 +310,11 @@ void verify_mfma_kernel(AttnArgs a) {
   float m[NT], l[NT];
   f32x4 acc[NT][8];
   // A reference that moves late, with the second walk it may need (see
-  // kLargeSum) -- except in the three-tile bf16 kernels, which lose more to the
+  // kLargeSum) -- except where bf16 windows of 9 to 13 tokens lose more to the
   // loop over the walks than they gain (8 x 12K, 9 tokens: 77.9 vs 74.3 us; 4 x
-  // 32K 94.6 vs 92.6).
-  constexpr bool kLate = KV == kFP8 || NT != 3;
+  // 32K 94.6 vs 92.6; 13 tokens, ~280K tokens in 8 equal sequences 221.9 vs 192.2,
+  // in 64 211.3 vs 194.8).
+  constexpr bool kLate = KV == kFP8 || NT <= 2 || (NT == 4 && !C4);
   float defer = kLate ? kDefer : 0.f;   // 0 in a second walk
   const int last_full = (L - a.q_len) / kPage;   // pages below this are fully visible to all rows
   // C4 tile: rows 16 (NT - 1) .. + 3 are the four heads of window token
